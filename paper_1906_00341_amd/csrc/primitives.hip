@@ -326,17 +326,22 @@ __global__ __launch_bounds__(BLOCK) void k_radix_scatter(const u64 *keys, u64 *o
     }
 }
 
+int64_t radix_tiles(int64_t n) { return ceil_div(n, RS_TILE); }
+
+void radix_pass_u64(const u64 *keys, u64 *out, int64_t n, int shift, uint32_t *start, hipStream_t s, Scratch &sc) {
+    const int64_t tiles = radix_tiles(n);
+    k_radix_hist<<<(unsigned)tiles, BLOCK, 0, s>>>(keys, n, shift, start, tiles);
+    scan_exclusive_u32(start, start, 256 * tiles, s, sc);
+    k_radix_scatter<<<(unsigned)tiles, BLOCK, 0, s>>>(keys, out, n, shift, start, tiles);
+}
+
 void radix_sort_u64(u64 *keys, u64 *tmp, int64_t n, int bits, hipStream_t s, Scratch &sc) {
     if (n <= 1 || bits <= 0) return;
-    int64_t tiles = ceil_div(n, RS_TILE);
-    uint32_t *counts = sc.get_n<uint32_t>(256 * tiles);
+    uint32_t *counts = sc.get_n<uint32_t>(256 * radix_tiles(n));
     u64 *a = keys, *b = tmp;
     int passes = (bits + 7) / 8;
     for (int p = 0; p < passes; p++) {
-        int shift = 8 * p;
-        k_radix_hist<<<(unsigned)tiles, BLOCK, 0, s>>>(a, n, shift, counts, tiles);
-        scan_exclusive_u32(counts, counts, 256 * tiles, s, sc);
-        k_radix_scatter<<<(unsigned)tiles, BLOCK, 0, s>>>(a, b, n, shift, counts, tiles);
+        radix_pass_u64(a, b, n, 8 * p, counts, s, sc);
         u64 *t = a; a = b; b = t;
     }
     if (a != keys) DSD_HIP(hipMemcpyAsync(keys, a, (size_t)n * sizeof(u64), hipMemcpyDeviceToDevice, s));

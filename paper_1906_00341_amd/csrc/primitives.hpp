@@ -44,6 +44,12 @@ void scan_exclusive_u32(const uint32_t *in, uint32_t *out, int64_t n, hipStream_
 // The result is in *keys; tmp has room for n keys.
 void radix_sort_u64(u64 *keys, u64 *tmp, int64_t n, int bits, hipStream_t s, Scratch &sc);
 
+// One stable counting pass: keys[0, n) grouped into out by the 8-bit digit at
+// shift.  start (256 * radix_tiles(n) counters): group q begins at
+// start[q * radix_tiles(n)].
+int64_t radix_tiles(int64_t n);
+void radix_pass_u64(const u64 *keys, u64 *out, int64_t n, int shift, uint32_t *start, hipStream_t s, Scratch &sc);
+
 // sum of a u64 array as a 128-bit (lo, hi) pair written to out[0], out[1] (device)
 void sum_u64_128(const u64 *in, int64_t n, u64 *out2, hipStream_t s, Scratch &sc);
 
