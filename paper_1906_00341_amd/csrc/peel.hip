@@ -1638,12 +1638,9 @@ __device__ u64 root_member_work(int x, const u64 *S, const u64 *mask, u64 *cnt, 
             if (L < take) {
                 const int y = q[L];
                 if constexpr (RR == 2) {
-                    if (role == 0) {
-                        atomicAdd(&cnt[y], 1ull);
-                        first += 1;
-                    } else {
-                        last += 1;
-                    }
+                    // an edge has no middle: y counts it as its own last member
+                    if (role == 0) first += 1;
+                    else last += 1;
                 } else if constexpr (RR == 3) {
                     // popcounts streamed over the words at and above y's
                     u64 cy = 0;
