@@ -146,15 +146,21 @@ def k4_bytes(st: dict, h: int) -> float:
 
 
 TAIL_KERNEL = "k_tail_engine"
+CLIQUE_TAIL_KERNEL = "k_ct_engine"
 
 
 def tail_kernel_bytes(st: dict) -> float:
-    """Algorithmic bytes of the tail engine (h = 2, 3) over one peel: every
+    """Algorithmic bytes of the tail over one peel.  Clique tail (h >= 4):
+    every member pair it tests, in its workgroups or on the grid, reads one
+    32-bit word of the adjacency matrix (4 B), every tail vertex its degree
+    and id in and its core number out (20 B).  Tail engine (h = 2, 3): every
     pair it walks is one 4-byte word of the rewritten rows; every tail vertex
     costs its degree and id in (8 + 4 B), its two row offsets (16 B), its id
     again and its core number out (4 + 8 B); every round handed to the grid
     costs each tail vertex its degree and state out (5 B) and back in with
     its row start (13 B)."""
+    if st.get("k4_main_kind") == 6:
+        return 4.0 * (st["k4_tail_pairs"] + st["k4_tail_grid_pairs"]) + 20.0 * st["k4_tail_vertices"]
     return (4.0 * st["k4_tail_pairs"] + 40.0 * st["k4_tail_vertices"]
             + 18.0 * st["k4_tail_vertices"] * st["k4_tail_grid_rounds"])
 
@@ -282,7 +288,7 @@ def run_workload(name: str, seed: int, steps: int, warmup: int, instrument: bool
         r2.update({"members_per_step": inst["k4_main_nbrs"]})
         cands.append(r2)
     if instrument and inst["k4_tail_launches"]:
-        t = roof(TAIL_KERNEL, name, inst["k4_tail_ms"], inst["k4_tail_launches"], tail_kernel_bytes(inst))
+        t = roof(CLIQUE_TAIL_KERNEL if kind == 6 else TAIL_KERNEL, name, inst["k4_tail_ms"], inst["k4_tail_launches"], tail_kernel_bytes(inst))
         t.update({"pairs_per_step": inst["k4_tail_pairs"], "tail_vertices": inst["k4_tail_vertices"],
                   "grid_rounds": inst["k4_tail_grid_rounds"], "grid_pairs": inst["k4_tail_grid_pairs"],
                   "grid_ms": inst["k4_tail_grid_ms"]})

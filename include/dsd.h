@@ -106,12 +106,18 @@ typedef struct {
      * its time (HIP events around every launch, with dsd_set_kernel_timing
      * on; else 0), launches (one per peel that reaches it, one more after
      * every grid round), the row pairs it walked (each clique among the tail
-     * vertices once per row) and the vertices it peeled */
+     * vertices once per row) and the vertices it peeled.  h >= 4: the clique
+     * tail (adjacency bitmaps, one workgroup per graph, at most 131072
+     * vertices): its time with all its kernels, its launch sequences, the
+     * member pairs its workgroups tested, and its vertices (again each time
+     * its matrix is rebuilt for those left) */
     double k4_tail_ms;
     uint64_t k4_tail_launches, k4_tail_pairs, k4_tail_vertices;
     /* the tail's rounds whose frontier rows hold more than 2^18 pairs, which
      * the engine hands to a kernel on every CU: their time (HIP events, with
-     * dsd_set_kernel_timing on; else 0), count and pairs */
+     * dsd_set_kernel_timing on; else 0), count and pairs.  h >= 4: the
+     * hand-overs to every CU and the member pairs tested there (no time of
+     * their own) */
     double k4_tail_grid_ms;
     uint64_t k4_tail_grid_rounds, k4_tail_grid_pairs;
     /* CoreExact's locate step (Section 6.1, Pruning1 and Pruning2), filled by
