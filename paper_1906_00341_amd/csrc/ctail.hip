@@ -14,11 +14,11 @@
 //     the live set, the frontier and a list of the lowest-degree vertices in
 //     LDS, and no launch in between.
 // A round too large for one workgroup is handed to every CU: the engine lists
-// its vertices and stops, k_ct_edges writes the adjacency of every C_v as
-// compact bitmap rows, k_ct_count counts and takes the losses off the
-// degrees, and the next engine launch ends the round.  The host enqueues
-// these three launches again and again without reading anything back but
-// the number of unfinished graphs now and then.
+// its vertices and stops, k_ct_front lists the members of every C_v,
+// k_ct_edges writes its adjacency as compact bitmap rows, k_ct_count counts
+// and takes the losses off the degrees, and the next engine launch ends the
+// round.  The host enqueues these four launches again and again without
+// reading anything back but the number of unfinished graphs now and then.
 //
 // Owner rule, levels and rounds are those of the round kernels: a round
 // removes every alive vertex of degree <= k; a clique with several of them is
@@ -37,7 +37,8 @@ namespace dsd {
 namespace {
 
 constexpr int64_t CT_MAX = 131072;             // alive vertices per graph (2,048-word rows: live sets of 16 KB in LDS)
-constexpr int64_t CT_SMALL = 16384;            // up to here a graph of a batch takes a 256-thread workgroup
+constexpr int64_t CT_SMALL = 4096;             // up to here a graph of a batch takes a 256-thread workgroup
+constexpr int64_t CT_MID = 32768;              // up to here its waves buffer whole matrix rows in LDS
 constexpr int64_t CT_MATRIX_WORDS = (int64_t)1 << 29;   // all matrices together (4 GiB)
 constexpr int64_t CT_ARENA_WORDS = (int64_t)1 << 25;    // compact rows of one handed-over round (256 MiB), at least
                                                         // one vertex's worth
@@ -45,10 +46,20 @@ constexpr int64_t CT_SHRINK_MIN = 4096;        // a matrix at least this wide is
 constexpr int64_t CT_VERTICES = (int64_t)1 << 23;       // vertices of all graphs together (items fit the counter)
 constexpr int CT_ITEM_SHIFT = 40;              // item counter above, task counter below in one 64-bit word
 constexpr u64 CT_TASK_MASK = (1ull << CT_ITEM_SHIFT) - 1ull;
-// One workgroup keeps a round whose vertices beyond 64 neighbours hold at
-// most this many member pairs (sum of |C_v|^2); the grid's two launches and
-// the engine's restart cost about 20 us, what one CU needs for 2^17 pairs.
-constexpr u64 CT_LIGHT_PAIRS = 1ull << 17;
+// One workgroup keeps a round of at most CT_FRONT frontier vertices whose
+// cost it puts at no more than CT_LIGHT: per vertex of d members, d matrix
+// rows of AW words (a cycle each) and d^2 member pairs (a quarter of a cycle
+// each; R > 3: d^3 / 64 for the counting).  The grid's three launches and the
+// engine's restart cost about as much (40 us).
+constexpr u64 CT_LIGHT = 100000;
+constexpr int CT_FRONT = 32;
+// Two waves per SIMD: what every wave does alike (the level, the frontier,
+// the control between barriers) is issued by each of them, so sixteen waves
+// take it twice as long; one wave per SIMD leaves the latency of its own
+// instructions open.  core of R-MAT scale 18, h = 4 / scale 16, h = 5: 256
+// threads 361 / 264 ms, 512 303 / 193 ms; 1,024 (an earlier form) 394 / 303.
+constexpr int CT_BLOCK = 512;
+constexpr int CT_VS = 64;                      // vertices of one LDS batch
 
 enum : int32_t { CT_ROUND = 0, CT_HEAVY = 1, CT_DONE = 2, CT_STOPPED = 3 };
 
@@ -61,12 +72,17 @@ struct CtGraph {
     u64 k, mu;
     int64_t n_alive, nF;  // nF: frontier of the round in progress
     int32_t nlevels, rounds, open, phase;
-    int32_t nheavy;       // frontier vertices still to be handed to the grid (hlist[hsel])
+    int32_t nheavy;       // frontier vertices the grid found no room for (hlist[hsel])
     int32_t hsel;
     u64 dest;             // cliques destroyed in this round, counted once per member besides their owner
+    u64 T;                // the candidate list across a hand-over: its threshold and vertices (cand);
+    int32_t ncand, pad;   // -1: none kept
 };
 
-// a vertex handed to the grid: its members' local ids and compact rows in the arena
+// a vertex handed to the grid, and (CtItem) its members' local ids and compact rows in the arena
+struct CtFront {
+    int32_t gi, v;
+};
 struct CtItem {
     int32_t gi, d, W, pad;
     u64 task0;            // first member task
@@ -75,6 +91,7 @@ struct CtItem {
 
 struct CtCtl {
     u64 count[2];                  // items << CT_ITEM_SHIFT | member tasks, by parity
+    int32_t nfront[2];             // vertices handed over
     unsigned long long atop[2];    // arena words handed out
     int32_t ndone;                 // graphs finished or stopped
     int32_t nstop;                 // stopped for a smaller matrix
@@ -90,58 +107,49 @@ struct CtBufs {
     u64 *M;               // matrices
     u64 *lb, *cb;         // live and current (frontier) sets between launches
     int32_t *hlist[2];
+    int32_t *cand;        // [vertices] candidate lists across hand-overs
     CtItem *items[2];
+    CtFront *front[2];
     u64 *arena;
     int64_t acap;
     int32_t R;            // h - 1: a removed vertex destroys the R-cliques of its C_v
     int32_t minpeel;
-    u64 light;
 };
 
 // words per compact row: at R >= 4 a width the counting is compiled for
 __host__ __device__ __forceinline__ int ct_words(int R, int d) {
     const int w = (d + 63) >> 6;
     if (R == 3) return w;
-    return w <= 2 ? 2 : w <= 4 ? 4 : w <= 8 ? 8 : w;
+    return w <= 2 ? 2 : w <= 4 ? 4 : w;
 }
 
 // ---------------------------------------------------------------- counting
 
-// word w (uniform) of the set M, without an indexed access to its registers
-template <int W>
-__device__ __forceinline__ u64 ct_pick(const u64 (&M)[W], int w) {
-    u64 v = M[0];
-#pragma unroll
-    for (int q = 1; q < W; q++) v = w == q ? M[q] : v;
-    return v;
-}
-
-// cliques of size D inside the set M (rank order); the sets stay in
-// registers (every index a constant), S: rows with stride ws
+// cliques of size D inside the set M (rank order), the loops over words
+// unrolled: an indexed access would move the sets out of registers; S: rows
+// with stride st
 template <int D, int W>
-__device__ __forceinline__ u64 ct_count_in(const u64 (&M)[W], const u64 *S, int ws) {
+__device__ __forceinline__ u64 ct_count_in(const u64 (&M)[W], const u64 *S, int st) {
+    u64 c = 0;
     if constexpr (D == 1) {
-        u64 c = 0;
 #pragma unroll
         for (int q = 0; q < W; q++) c += (u64)__popcll(M[q]);
-        return c;
     } else {
-        u64 tot = 0;
-#pragma unroll 1
+#pragma unroll
         for (int w = 0; w < W; w++) {
-            u64 word = ct_pick<W>(M, w);
+            u64 word = M[w];
             while (word) {
                 const int bit = __builtin_ctzll(word);
                 word &= word - 1;
-                const u64 *row = S + (size_t)(w * 64 + bit) * ws;
+                const u64 *row = S + (w * 64 + bit) * st;
                 u64 M2[W];
 #pragma unroll
                 for (int q = 0; q < W; q++) M2[q] = q < w ? 0ull : ((q == w ? word : M[q]) & row[q]);   // above the bit
-                tot += ct_count_in<D - 1, W>(M2, S, ws);
+                c += ct_count_in<D - 1, W>(M2, S, st);
             }
         }
-        return tot;
     }
+    return c;
 }
 
 __device__ __forceinline__ u64 bcast64(u64 v, int src) {
@@ -150,14 +158,14 @@ __device__ __forceinline__ u64 bcast64(u64 v, int src) {
     return ((u64)hi << 32) | lo;
 }
 
-// The R-cliques of the set {0 .. d-1} (rows S, stride ws, W words, symmetric)
-// that hold member i, on one wave: the (R-1)-cliques among its neighbours.
-// Lane j of each 64 takes neighbour y = 64 q + j.
+// The R-cliques (R >= 4) of the set with rows S (stride st, W words,
+// symmetric) that hold member i, on one wave: the (R-1)-cliques among its
+// neighbours.  Lane j of each 64 takes neighbour y = 64 q + j.
 template <int R, int W>
-__device__ __forceinline__ u64 ct_member_small(int i, int d, const u64 *S, int ws) {
+__device__ __forceinline__ u64 ct_member_small(int i, const u64 *S, int st) {
     const int L = lane();
     u64 N[W];
-    const u64 mine = L < W ? S[(size_t)i * ws + L] : 0ull;
+    const u64 mine = L < W ? S[(size_t)i * st + L] : 0ull;
 #pragma unroll
     for (int q = 0; q < W; q++) N[q] = bcast64(mine, q);
     u64 c = 0;
@@ -165,23 +173,15 @@ __device__ __forceinline__ u64 ct_member_small(int i, int d, const u64 *S, int w
     for (int q = 0; q < W; q++) {
         const u64 nq = bcast64(mine, q);
         if ((nq >> L) & 1ull) {
-            const u64 *row = S + (size_t)(q * 64 + L) * ws;
+            const u64 *row = S + (size_t)(q * 64 + L) * st;
+            const u64 above = L == 63 ? 0ull : (~0ull << (L + 1));
             u64 M2[W];
-            if constexpr (R == 3) {
-                // every pair of adjacent neighbours from both its ends
 #pragma unroll
-                for (int w = 0; w < W; w++) M2[w] = N[w] & row[w];
-                c += ct_count_in<1, W>(M2, S, ws);
-            } else {
-                const u64 above = L == 63 ? 0ull : (~0ull << (L + 1));
-#pragma unroll
-                for (int w = 0; w < W; w++) M2[w] = w < q ? 0ull : (N[w] & row[w] & (w == q ? above : ~0ull));
-                c += ct_count_in<R - 2, W>(M2, S, ws);
-            }
+            for (int w = 0; w < W; w++) M2[w] = w < q ? 0ull : (N[w] & row[w] & (w == q ? above : ~0ull));
+            c += ct_count_in<R - 2, W>(M2, S, st);
         }
     }
-    c = wave_sum(c);
-    return R == 3 ? c / 2 : c;
+    return wave_sum(c);
 }
 
 // The set bits of the words M (word w in lane w of every lane group of Wp
@@ -313,10 +313,12 @@ __global__ __launch_bounds__(BLOCK) void k_ct_edges(CtBufs q, int par) {
     const u64 ntask = cnt & CT_TASK_MASK;
     const CtItem *items = q.items[par];
     const int wv = threadIdx.x / WAVE, L = lane();
+    u64 pairs = 0;
     for (u64 t = (u64)blockIdx.x * WAVES_PER_BLOCK + wv; t < ntask; t += (u64)gridDim.x * WAVES_PER_BLOCK) {
         const CtItem it = items[ct_item_of(items, nitems, t)];
         const CtGraph &cg = q.cg[it.gi];
         const int i = (int)(t - it.task0), d = it.d, W = it.W;
+        pairs += (u64)d;
         const int32_t *C = (const int32_t *)(q.arena + it.off);
         u64 *row = q.arena + it.off + (d + 1) / 2 + (int64_t)i * W;
         const uint32_t *Mx = (const uint32_t *)(q.M + cg.moff + (int64_t)C[i] * cg.AW);
@@ -339,6 +341,7 @@ __global__ __launch_bounds__(BLOCK) void k_ct_edges(CtBufs q, int par) {
             if (L < 8 && w0 + L < W) row[w0 + L] = mine;
         }
     }
+    if (L == 0 && pairs) atomicAdd(&q.ctl->hpairs, pairs);
 }
 
 // One wave per member: the cliques of its vertex that hold it, taken off its degree.
@@ -356,14 +359,14 @@ __global__ __launch_bounds__(BLOCK) void k_ct_count(CtBufs q, int par) {
     const int wv = threadIdx.x / WAVE, L = lane();
     for (u64 t = (u64)blockIdx.x * WAVES_PER_BLOCK + wv; t < ntask; t += (u64)gridDim.x * WAVES_PER_BLOCK) {
         const CtItem it = items[ct_item_of(items, nitems, t)];
-        const CtGraph &cg = q.cg[it.gi];
+        CtGraph &cg = q.cg[it.gi];
+        const bool keep = cg.ncand >= 0;              // (only grows while >= 0)
         const int i = (int)(t - it.task0), d = it.d, W = it.W;
         const int32_t x = ((const int32_t *)(q.arena + it.off))[i];
         const u64 *S = q.arena + it.off + (d + 1) / 2;
         u64 c;
-        if (W <= 2 && R > 3) c = ct_member_small<R, 2>(i, d, S, W);
-        else if (W == 4 && R > 3) c = ct_member_small<R, 4>(i, d, S, W);
-        else if (W == 8 && R > 3) c = ct_member_small<R, 8>(i, d, S, W);
+        if (R > 3 && W <= 2) c = ct_member_small<R, 2>(i, S, W);
+        else if (R > 3 && W <= 4) c = ct_member_small<R, 4>(i, S, W);
         else if (W <= 64) {
             int lw = 0;
             while ((1 << lw) < W) lw++;
@@ -374,7 +377,12 @@ __global__ __launch_bounds__(BLOCK) void k_ct_count(CtBufs q, int par) {
             const u64 *p[1] = {S + (size_t)i * W};
             c = wave_sum(ct_huge<R - 1, 1>(p, -1, S, W)) / 2;
         }
-        if (L == 0 && c) atomic_sub_u64(&q.ldeg[cg.base + x], c);
+        // (a removed vertex's degree slot holds its label)
+        if (L == 0 && c && !((q.cb[cg.boff + (x >> 6)] >> (x & 63)) & 1ull)) {
+            const u64 old = atomic_sub_u64(&q.ldeg[cg.base + x], c);
+            // a vertex that crosses the threshold becomes a candidate (once: degrees only fall)
+            if (keep && old > cg.T && old - c <= cg.T) q.cand[cg.base + atomicAdd(&cg.ncand, 1)] = x;
+        }
         if (it.gi != tg) {
             if (L == 0 && tally) atomicAdd(&q.cg[tg].dest, tally);
             tg = it.gi;
@@ -400,12 +408,114 @@ __global__ __launch_bounds__(BLOCK) void k_ct_count(CtBufs q, int par) {
         }
 }
 
+// the members of v's candidate set in word w of its matrix row m: live, not a frontier vertex of rank <= v
+__device__ __forceinline__ u64 ct_cand(u64 m, u64 live, u64 cur, int32_t v, int w) {
+    const int vw = v >> 6;
+    if (w > vw) cur = 0;
+    else if (w == vw) cur &= (v & 63) == 63 ? ~0ull : ((2ull << (v & 63)) - 1ull);
+    return m & live & ~cur;
+}
+
+// One wave per handed-over vertex: its members' ids to the arena, and an
+// item with one task per member; a vertex without room goes back to its
+// graph's list for the next sequence (the first one always finds room).
+__global__ __launch_bounds__(BLOCK) void k_ct_front(CtBufs q, int par) {
+    const int nf = q.ctl->nfront[par], L = lane();
+    for (int f = blockIdx.x * WAVES_PER_BLOCK + threadIdx.x / WAVE; f < nf; f += gridDim.x * WAVES_PER_BLOCK) {
+        const CtFront fr = q.front[par][f];
+        CtGraph &cg = q.cg[fr.gi];
+        const int32_t v = fr.v, AW = cg.AW;
+        const u64 *row = q.M + cg.moff + (int64_t)v * AW, *lb = q.lb + cg.boff, *cb = q.cb + cg.boff;
+        int c = 0;
+        for (int w = L; w < AW; w += WAVE) c += __popcll(ct_cand(row[w], lb[w], cb[w], v, w));
+        const int d = wave_sum(c);
+        if (d < q.R) continue;
+        const int W = ct_words(q.R, d);
+        const int64_t words = (d + 1) / 2 + (int64_t)d * W;
+        int64_t off = -1;
+        if (L == 0) {
+            off = (int64_t)atomicAdd(&q.ctl->atop[par], (unsigned long long)words);
+            if (off + words <= q.acap) {
+                const u64 old = atomicAdd(&q.ctl->count[par], (1ull << CT_ITEM_SHIFT) | (u64)d);
+                q.items[par][old >> CT_ITEM_SHIFT] = CtItem{fr.gi, d, W, 0, old & CT_TASK_MASK, off};
+            } else {
+                off = -1;
+                q.hlist[cg.hsel ^ 1][cg.base + atomicAdd(&cg.nheavy, 1)] = v;
+            }
+        }
+        off = __shfl(off, 0, WAVE);
+        if (off < 0) continue;
+        int32_t *C = (int32_t *)(q.arena + off);
+        int run = 0;
+        for (int w0 = 0; w0 < AW; w0 += WAVE) {
+            const int w = w0 + L;
+            u64 m = w < AW ? ct_cand(row[w], lb[w], cb[w], v, w) : 0ull;
+            const int pc = __popcll(m);
+            const int inc = wave_incl_scan(pc);
+            int o = run + inc - pc;
+            while (m) {
+                C[o++] = w * 64 + __builtin_ctzll(m);
+                m &= m - 1;
+            }
+            run += __shfl(inc, WAVE - 1, WAVE);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- the engine
 
-// a graph's degrees are touched by its own workgroup only while the engine
-// runs: the subtraction needs no wider scope, the load must pass the L1
+// Wave reductions in VALU cross-lane operations (DPP): quad permutations and
+// row mirrors reduce every 16-lane row, row broadcasts join the rows, lane 63
+// ends with the total.
+template <int CTRL, int MASK>
+__device__ __forceinline__ int ct_dpp(int id, int v) {
+    return __builtin_amdgcn_update_dpp(id, v, CTRL, MASK, 0xf, false);
+}
+__device__ __forceinline__ int ct_wave_sum(int v) {
+    v += ct_dpp<0xb1, 0xf>(0, v);
+    v += ct_dpp<0x4e, 0xf>(0, v);
+    v += ct_dpp<0x141, 0xf>(0, v);
+    v += ct_dpp<0x140, 0xf>(0, v);
+    v += ct_dpp<0x142, 0xa>(0, v);
+    v += ct_dpp<0x143, 0xc>(0, v);
+    return __builtin_amdgcn_readlane(v, 63);
+}
+template <int CTRL, int MASK>
+__device__ __forceinline__ u64 ct_min_step(u64 v) {
+    const uint32_t lo = (uint32_t)ct_dpp<CTRL, MASK>(-1, (int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)ct_dpp<CTRL, MASK>(-1, (int)(uint32_t)(v >> 32));
+    const u64 o = ((u64)hi << 32) | lo;
+    return o < v ? o : v;
+}
+__device__ __forceinline__ u64 ct_wave_min(u64 v) {
+    v = ct_min_step<0xb1, 0xf>(v);
+    v = ct_min_step<0x4e, 0xf>(v);
+    v = ct_min_step<0x141, 0xf>(v);
+    v = ct_min_step<0x140, 0xf>(v);
+    v = ct_min_step<0x142, 0xa>(v);
+    v = ct_min_step<0x143, 0xc>(v);
+    return bcast64(v, 63);
+}
+// exclusive prefix of a count 0 .. 64 over the wave's lanes, one ballot per bit
+__device__ __forceinline__ int ct_wave_prefix(int v) {
+    int pre = 0;
+    const u64 lt = lanemask_lt();
+#pragma unroll
+    for (int bit = 0; bit < 7; bit++) pre += __popcll(__ballot((v >> bit) & 1) & lt) << bit;
+    return pre;
+}
+
+// workgroup barrier that orders LDS only: global stores (core numbers) stay
+// in flight across it; the degrees' atomics have returned by then
+__device__ __forceinline__ void ct_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// a graph's degrees are touched by its own workgroup only while the engine runs
 __device__ __forceinline__ u64 ct_load_deg(const u64 *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ u64 ct_sub_deg(u64 *p, u64 c) {
     return __hip_atomic_fetch_add(p, (u64)0 - c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -425,34 +535,310 @@ __device__ __forceinline__ u64 ct_bin_top(int b) {
     return ((u64)(9 + (b & 7)) << (e - 3)) - 1ull;     // (bin 503: the top wraps to 2^64 - 1)
 }
 
+// The edges (x, y), x < y, of the queue's codes (x << 16 | y, members of one
+// vertex: rows at S, stride st), a lane each, R >= 4: every triangle (x, y, z),
+// z above y, gives its corners the (R-3)-cliques of their common neighbours,
+// so a member ends with C(R-1, 2) times its cliques.  (By edges alone a row
+// would be read once for every z on either side: three times as many reads.)
+template <int R, int W>
+__device__ __forceinline__ void ct_edge_drain(const uint32_t *qu, int take, const u64 *S, int st, u64 *cnt) {
+    const int L = lane();
+    if (L < take) {
+        const uint32_t code = qu[L];
+        const int x = (int)(code >> 16), y = (int)(code & 0xffffu);
+        u64 M[W], sum = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) M[w] = S[x * st + w] & S[y * st + w];
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            u64 word = M[w] & ct_above(w, y);
+            while (word) {
+                // ZB corners at once: their rows are in flight together
+                constexpr int ZB = W <= 2 ? 4 : 2;
+                int z[ZB];
+                u64 row[ZB][W];
+#pragma unroll
+                for (int u = 0; u < ZB; u++) {
+                    z[u] = word ? w * 64 + __builtin_ctzll(word) : -1;
+                    word &= word - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < ZB; u++)
+#pragma unroll
+                    for (int q = 0; q < W; q++) row[u][q] = S[max(z[u], 0) * st + q];
+#pragma unroll
+                for (int u = 0; u < ZB; u++) {
+                    if (u > 0 && z[u] < 0) break;
+                    u64 M2[W];
+#pragma unroll
+                    for (int q = 0; q < W; q++) M2[q] = M[q] & row[u][q];
+                    const u64 c = ct_count_in<R - 3, W>(M2, S, st);
+                    if (c) {
+                        atomicAdd(&cnt[z[u]], c);
+                        sum += c;
+                    }
+                }
+            }
+        }
+        if (sum) {
+            atomicAdd(&cnt[x], sum);
+            atomicAdd(&cnt[y], sum);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// R = 3: twice the triangles of the set that hold members i0 .. i0 + MB - 1, on
+// one wave: for every neighbour y (a lane each) the neighbours it shares with
+// the member.  y's row is read once for all MB members.
+template <int W, int MB>
+__device__ __forceinline__ void ct_member_tri(int i0, int n, int d, const u64 *S, int st, u64 *cnt) {
+    const int L = lane();
+    const u64 mine = S[(i0 + min(L / W, n - 1)) * st + L % W];
+    u64 N[MB][W];
+    uint32_t c[MB];
+#pragma unroll
+    for (int m = 0; m < MB; m++) {
+        c[m] = 0;
+#pragma unroll
+        for (int q = 0; q < W; q++) N[m][q] = bcast64(mine, m * W + q);
+    }
+#pragma unroll
+    for (int q = 0; q < W; q++) {
+        u64 row[W];
+        const u64 *y = S + min(q * 64 + L, d - 1) * st;
+#pragma unroll
+        for (int w = 0; w < W; w++) row[w] = y[w];
+#pragma unroll
+        for (int m = 0; m < MB; m++) {
+            uint32_t s = 0;
+#pragma unroll
+            for (int w = 0; w < W; w++) s += (uint32_t)__popcll(N[m][w] & row[w]);
+            c[m] += (N[m][q] >> L) & 1ull ? s : 0u;
+        }
+    }
+    int tot = 0;
+#pragma unroll
+    for (int m = 0; m < MB; m++) {
+        const int s = ct_wave_sum((int)c[m]);
+        tot = L == m ? s : tot;
+    }
+    if (L < n) cnt[i0 + L] = (u64)(uint32_t)tot;
+}
+
+// The same for a vertex of more than 64 members: row sums of A o A^2 (A its
+// members' 0/1 adjacency), a contraction, on the matrix cores.  A unit is a
+// column block J of 32 members: C = A[I] A[J]^T by 32 x 32 x 32 products of
+// bytes for every row block I, then every lane adds its column's entries
+// where A holds a 1.  Bits become bytes by a multiplication (four at a time);
+// A is symmetric, so both operands read rows, and the order of the k index
+// does not matter as long as it is the same for both.  Rows past the last
+// member repeat it; their products meet zero bits only.
+// d = 256: popcounts (four words a pair, lanes half idle) 62,000 cycles on one CU, these products 10,000.
+typedef int ct_i4 __attribute__((ext_vector_type(4)));
+typedef int ct_i16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ ct_i4 ct_bytes(uint32_t bits) {
+    ct_i4 v;
+#pragma unroll
+    for (int u = 0; u < 4; u++) v[u] = (int)((((bits >> (4 * u)) & 15u) * 0x00204081u) & 0x01010101u);
+    return v;
+}
+template <int TMAX>
+__device__ __forceinline__ void ct_tri_block(int J, int d, const u64 *S, int st, u64 *cnt) {
+    const int L = lane(), lo = L & 31, sh = (L >> 5) * 16;
+    const uint32_t *S32 = (const uint32_t *)S;
+    const int T = (d + 31) >> 5;
+    const int j = J * 32 + lo, jr = min(j, d - 1) * 2 * st;
+    ct_i4 bj[TMAX];
+#pragma unroll
+    for (int k = 0; k < TMAX; k++)
+        if (k < T) bj[k] = ct_bytes(S32[jr + k] >> sh);
+    uint32_t sum = 0;
+    for (int I = 0; I < T; I++) {
+        const int ir = min(I * 32 + lo, d - 1) * 2 * st;
+        const uint32_t mask = S32[jr + I] >> (4 * (L >> 5));   // register r holds row 8 (r / 4) + 4 (lane / 32) + r % 4
+        ct_i16 acc = {};
+#pragma unroll
+        for (int k = 0; k < TMAX; k++)
+            if (k < T) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(ct_bytes(S32[ir + k] >> sh), bj[k], acc, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 16; r++) sum += (uint32_t)acc[r] & (0u - ((mask >> (8 * (r / 4) + r % 4)) & 1u));
+    }
+    if (j < d && sum) atomicAdd(&cnt[j], (u64)sum);
+}
+
+// words of a member's compact row in LDS, and their stride: odd beyond one
+// word, so that the lanes' rows spread over the banks
+__device__ __forceinline__ int ct_lds_words(int d) {
+    const int W = (d + 63) >> 6;
+    return W <= 2 ? W : W <= 4 ? 4 : 8;
+}
+__device__ __forceinline__ int ct_lds_stride(int Wt) { return Wt > 1 ? Wt + 1 : 1; }
+
+// one batch of frontier vertices in LDS
+struct CtBatch {
+    u64 *S;               // the members' compact rows
+    const int32_t *id;    // members, one vertex's after another
+    const int32_t *vm, *vd, *vr;   // a vertex's first member, members, first row word
+};
+
+// The members' compact rows.  The words of a member's matrix row that hold
+// members' columns (wlo on: the local ids follow the degree order, and the
+// members of a low vertex are mostly hubs) are read coalesced, NWR a lane,
+// laid into the wave's LDS buffer, and the members' bits gathered there:
+// gathering from memory costs the CU about 36 cycles per 64 members whatever
+// the row's width.  RB rows of one vertex go through together, the next RB
+// are in flight meanwhile; the waves take such groups in turn.  While the
+// matrix exceeds the XCD's L2 the one CU's misses bound this (about 8 bytes a
+// cycle); then its instructions do.  Indexes are clamped rather than loads
+// predicated: a predicated load gets a branch and a wait of its own.
+constexpr int ct_rows_together(int nwr) { return nwr <= 2 ? 8 : 16 / nwr; }
+template <int NWR, int WMAXT, int NW>
+__device__ __forceinline__ void ct_rows_vertex(const CtBatch &B, int vm, int vd, int vr, int c0, const u64 *M, int AW,
+                                               int wlo, u64 *buf) {
+    constexpr int RB = ct_rows_together(NWR), BW = NWR * WAVE;
+    const int L = lane();
+    const uint32_t *b32 = (const uint32_t *)buf;
+    int col[NWR];
+#pragma unroll
+    for (int c = 0; c < NWR; c++) col[c] = min(wlo + c * WAVE + L, AW - 1);
+    // this lane's columns: word offset in the buffer, bit, and the lanes that hold one
+    int off[WMAXT], sh[WMAXT];
+    u64 have[WMAXT];
+    const int Wt = ct_lds_words(vd), st = ct_lds_stride(Wt);
+#pragma unroll
+    for (int w = 0; w < WMAXT; w++) {
+        const int32_t id = B.id[vm + min(w * WAVE + L, vd - 1)];
+        off[w] = (id >> 5) - 2 * wlo;
+        sh[w] = id & 31;
+        have[w] = __ballot(w * WAVE + L < vd);
+    }
+    u64 r[RB][NWR];
+    auto fetch = [&](int s0) {
+        int64_t x[RB];
+#pragma unroll
+        for (int u = 0; u < RB; u++) x[u] = B.id[vm + min(s0 + u, vd - 1)];
+#pragma unroll
+        for (int u = 0; u < RB; u++)
+#pragma unroll
+            for (int c = 0; c < NWR; c++) r[u][c] = M[x[u] * AW + col[c]];
+    };
+    fetch(c0 * RB);
+    for (int s0 = c0 * RB; s0 < vd; s0 += NW * RB) {
+#pragma unroll
+        for (int u = 0; u < RB; u++)
+#pragma unroll
+            for (int c = 0; c < NWR; c++) buf[u * BW + c * WAVE + L] = r[u][c];
+        __builtin_amdgcn_wave_barrier();
+        if (s0 + NW * RB < vd) fetch(s0 + NW * RB);
+        u64 mine[RB];
+#pragma unroll
+        for (int u = 0; u < RB; u++) mine[u] = 0;
+#pragma unroll
+        for (int w = 0; w < WMAXT; w++) {
+            if (w >= Wt) break;
+            uint32_t v[RB];
+#pragma unroll
+            for (int u = 0; u < RB; u++) v[u] = b32[u * BW * 2 + off[w]];
+#pragma unroll
+            for (int u = 0; u < RB; u++) {
+                const u64 bw = __ballot((v[u] >> sh[w]) & 1u) & have[w];
+                mine[u] = L == w ? bw : mine[u];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < RB; u++)
+            if (L < Wt && s0 + u < vd) B.S[vr + (s0 + u) * st + L] = mine[u];
+    }
+}
+template <int NWR, int NW>
+__device__ __forceinline__ int ct_rows_do(const CtBatch &B, int vm, int vd, int vr, int first, const u64 *M, int AW,
+                                           int wlo, u64 *buf) {
+    constexpr int RB = ct_rows_together(NWR);
+    const int chunks = (vd + RB - 1) / RB;
+    if (first < chunks) {
+        if (vd <= 64) ct_rows_vertex<NWR, 1, NW>(B, vm, vd, vr, first, M, AW, wlo, buf);
+        else if (vd <= 256) ct_rows_vertex<NWR, 4, NW>(B, vm, vd, vr, first, M, AW, wlo, buf);
+        else ct_rows_vertex<NWR, 8, NW>(B, vm, vd, vr, first, M, AW, wlo, buf);
+    }
+    return chunks;
+}
+// every vertex of the batch; WB: words of the longest row (0: no buffer, straight from memory)
+template <int WB, int NW>
+__device__ __forceinline__ void ct_rows(const CtBatch &B, int nv, const u64 *M, int AW, u64 *buf) {
+    const int wv = threadIdx.x / WAVE, L = lane();
+    const int lm = B.vm[L], ld = B.vd[L], lr = B.vr[L];        // (CT_VS = 64: a lane per vertex)
+    int turn = wv;                                             // groups until this wave's next
+    for (int vi = 0; vi < nv; vi++) {
+        const int vm = __builtin_amdgcn_readlane(lm, vi), vd = __builtin_amdgcn_readlane(ld, vi),
+                  vr = __builtin_amdgcn_readlane(lr, vi);
+        const int wlo = __builtin_amdgcn_readfirstlane(B.id[vm]) >> 6, span = AW - wlo;
+        int chunks;
+        if constexpr (WB == 0) {
+            // straight from memory: rows too long for a buffer (few rounds: most go to the grid)
+            const int Wt = ct_lds_words(vd), st = ct_lds_stride(Wt);
+            chunks = vd;
+            for (int i = turn; i < vd; i += NW) {
+                const uint32_t *x = (const uint32_t *)(M + (int64_t)B.id[vm + i] * AW);
+                u64 mine = 0;
+                for (int w = 0; w < Wt; w++) {
+                    const int32_t id = B.id[vm + min(w * WAVE + L, vd - 1)];
+                    const u64 bw = __ballot(((x[id >> 5] >> (id & 31)) & 1u) && w * WAVE + L < vd);
+                    mine = L == w ? bw : mine;
+                }
+                if (L < Wt) B.S[vr + i * st + L] = mine;
+            }
+        } else if (WB <= 64 || span <= 64) {
+            chunks = ct_rows_do<1, NW>(B, vm, vd, vr, turn, M, AW, wlo, buf);
+        } else if (span <= 128) {
+            chunks = ct_rows_do<2, NW>(B, vm, vd, vr, turn, M, AW, wlo, buf);
+        } else if (span <= 256) {
+            chunks = ct_rows_do<4, NW>(B, vm, vd, vr, turn, M, AW, wlo, buf);
+        } else {
+            chunks = ct_rows_do<8, NW>(B, vm, vd, vr, turn, M, AW, wlo, buf);
+        }
+        turn = (turn - chunks) & (NW - 1);                     // (NW a power of two)
+    }
+}
+
 // One workgroup per graph.  CC: capacity of the candidate list, which holds
 // every alive vertex of degree <= T (T raised when it runs dry): a round reads
-// its degrees only.  DC: members of a C_v whose compact rows fit the LDS.
-// AMAX: vertices of a graph.  A round is three workgroup barriers and about
-// four dependent trips to L2 when its frontier has at most 64 neighbours
-// each (a wave per vertex), four more barriers per larger vertex.
-template <int BT, int CC, int DC, int AMAX, int R>
-__global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const int32_t *glist, int par, int64_t shrink_at) {
-    constexpr int NW = BT / WAVE, WMAX = AMAX / 64, CPT = CC / BT, DW = DC / 64, DS = DW | 1;
+// its degrees only.  SLOTS, ROWW, DC: members and row words of one batch of
+// frontier vertices in LDS, members of one vertex.  AMAX: vertices of a graph.
+// A round is six workgroup barriers and four dependent trips to L2: the
+// candidates' degrees, the frontier's matrix rows, the members' rows, the
+// degrees' atomics.
+// WB: words of a matrix row that fit a wave's buffer (0: rows are not buffered).
+template <int CC, int SLOTS, int ROWW, int AMAX, int WB, int R>
+__global__ __launch_bounds__(CT_BLOCK) void k_ct_engine(PeelBufs b, CtBufs q, const int32_t *glist, int par, int64_t shrink_at) {
+    constexpr int BT = CT_BLOCK, NW = BT / WAVE, WMAX = AMAX / 64, CPT = CC / BT;
+    constexpr int DC = (R > 3 || SLOTS < 1024) ? 256 : 512;   // (R > 3: four-word sets in registers)
+    static_assert(DC <= SLOTS && DC * (DC / 64 + 1) <= ROWW, "one vertex of DC members fits a batch");
+    static_assert(WB == 0 || WB == WMAX, "a buffer holds the longest row");
     __shared__ u64 sLive[WMAX], sCur[WMAX];
     __shared__ int32_t sCand[2][CC], sF[CC];
-    __shared__ u64 sS[DC * DS];
-    __shared__ int32_t sC[DC];
-    __shared__ u64 sCnt[DC];
-    __shared__ int32_t sWC[NW][64];
-    __shared__ u64 sWS[NW][64];
+    __shared__ u64 sS[ROWW];                       // compact rows, stride W + 1 (W > 1): odd, so lanes' rows spread over the banks
+    __shared__ int32_t sId[SLOTS];                 // the batch's members, its vertices' one after another
+    __shared__ u64 sCnt[SLOTS];
+    __shared__ int32_t sVm[CT_VS], sVd[CT_VS], sVr[CT_VS];
+    __shared__ uint32_t sQ[NW][R > 3 ? 2 * WAVE : 1];
+    __shared__ u64 sRow[NW][WB > 64 ? 1024 : WB > 0 ? 512 : 1];   // eight rows of 64 words, down to two of 512
     __shared__ u64 sMin[NW];
-    __shared__ int32_t sWsum[NW];
+    __shared__ u64 sAlloc[2];                      // vertices << 48 | members << 24 | row words, by batch parity
+    __shared__ int32_t sSlots[2], sNv[2], sNext, sPend[2];
     __shared__ int32_t sN[2];                      // candidates of either list
-    __shared__ int32_t sNF[2], sNfl[2], sNH[2];    // frontier, frontier with cliques, vertices beyond one wave
+    __shared__ int32_t sNF[2], sNfl[2], sNH[2];    // frontier, frontier with cliques, vertices for the grid
     __shared__ u64 sDest[2], sPairs[2];
-    __shared__ int32_t sMaxD[2], sTook;
+    __shared__ uint32_t sHist[CT_BINS];
+    __shared__ int32_t sAt, sYield;
     const int gi = glist ? glist[blockIdx.x] : (int)blockIdx.x;
     const int t = threadIdx.x, wv = t / WAVE, L = lane();
     if (blockIdx.x == 0 && t == 0) {
         // the other parity's hand-over has been consumed by the launches before this one
         q.ctl->count[par ^ 1] = 0;
         q.ctl->atop[par ^ 1] = 0;
+        q.ctl->nfront[par ^ 1] = 0;
     }
     CtGraph &cg = q.cg[gi];
     int32_t phase = cg.phase;
@@ -471,32 +857,26 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
     }
     if (t < 2) {
         sN[t] = 0;
-        sNF[t] = sNfl[t] = sNH[t] = sMaxD[t] = 0;
-        sDest[t] = sPairs[t] = 0;
+        sNF[t] = sNfl[t] = sNH[t] = sPend[t] = sSlots[t] = sNv[t] = 0;
+        sDest[t] = sPairs[t] = sAlloc[t] = 0;
+    }
+    if (phase == CT_HEAVY) hsel ^= 1;              // what the grid sent back
+    __syncthreads();
+    const CtBatch batch{sS, sId, sVm, sVd, sVr};
+    u64 T = 0, work = 0;
+    u64 dest = phase == CT_HEAVY ? cg.dest : 0;
+    bool rescan = true;
+    int cb = 0, p = 0, turn = 0;
+    int32_t kept = phase == CT_HEAVY ? cg.ncand : -1;   // candidates kept across the hand-over
+    if (kept > CC) kept = -1;
+    if (kept >= 0) {
+        T = cg.T;
+        for (int i = t; i < kept; i += BT) sCand[0][i] = q.cand[base + i];
+        if (t == 0) sN[0] = kept;
     }
     __syncthreads();
-    u64 T = 0, work = 0;
-    u64 dest = phase == CT_HEAVY ? __hip_atomic_load(&cg.dest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
-    bool rescan = true;
-    int cb = 0, p = 0;
     int64_t guard = 0;
-
-    // the members of v's candidate set in word w: live, not a frontier vertex of rank <= v
-    auto cand_word = [&](int32_t v, int w) -> u64 {
-        const u64 m = M[(int64_t)v * AW + w];
-        const int vw = v >> 6;
-        u64 own = sCur[w];
-        if (w > vw) own = 0;
-        else if (w == vw) own &= (v & 63) == 63 ? ~0ull : ((2ull << (v & 63)) - 1ull);
-        return m & sLive[w] & ~own;
-    };
-    auto apply = [&](int32_t x, u64 c) {
-        const u64 old = ct_sub_deg(&ldeg[x], c);
-        if (old > T && old - c <= T) {
-            const int pos = atomicAdd(&sN[cb ^ 1], 1);
-            if (pos < CC) sCand[cb ^ 1][pos] = x;
-        }
-    };
+    bool fresh = false;                             // the round in progress left a candidate list
 
     while (true) {
         if (++guard > 4 * (int64_t)A + 64) {        // every pass ends a round or hands vertices over
@@ -506,62 +886,23 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
         }
         if (phase == CT_HEAVY) {
             if (nheavy > 0) {
-                // hand the listed vertices to the grid: members and a place for
-                // their rows; those that find no room wait for the next launch
-                if (t == 0) sTook = 0;
+                // hand the listed vertices to the grid, and keep the candidates
+                // (list cb ^ 1 holds the round's survivors and newcomers)
+                if (!fresh) kept = -1;
+                else kept = sN[cb ^ 1] <= CC ? sN[cb ^ 1] : -1;
+                for (int i = t; i < kept; i += BT) q.cand[base + i] = sCand[cb ^ 1][i];
+                if (t == 0) sAt = atomicAdd(&q.ctl->nfront[par], nheavy);
                 __syncthreads();
-                const int32_t *in = q.hlist[hsel] + base;
-                int32_t *left = q.hlist[hsel ^ 1] + base;
-                for (int j = wv; j < nheavy; j += NW) {
-                    const int32_t v = in[j];
-                    int c = 0;
-                    for (int w = L; w < AW; w += WAVE) c += __popcll(cand_word(v, w));
-                    const int d = wave_sum(c);
-                    if (d < R) continue;
-                    const int W = ct_words(R, d);
-                    const int64_t words = (d + 1) / 2 + (int64_t)d * W;
-                    int64_t off = -1;
-                    int idx = -1;
-                    u64 tb = 0;
-                    if (L == 0) {
-                        off = (int64_t)atomicAdd(&q.ctl->atop[par], (unsigned long long)words);
-                        if (off + words <= q.acap) {
-                            const u64 old = atomicAdd(&q.ctl->count[par], (1ull << CT_ITEM_SHIFT) | (u64)d);
-                            idx = (int)(old >> CT_ITEM_SHIFT);
-                            tb = old & CT_TASK_MASK;
-                            q.items[par][idx] = CtItem{gi, d, W, 0, tb, off};
-                            work += (u64)d * (u64)d;
-                        } else {
-                            left[atomicAdd(&sTook, 1)] = v;
-                        }
-                    }
-                    idx = __shfl(idx, 0, WAVE);
-                    if (idx < 0) continue;
-                    off = __shfl(off, 0, WAVE);
-                    int32_t *C = (int32_t *)(q.arena + off);
-                    int run = 0;
-                    for (int w0 = 0; w0 < AW; w0 += WAVE) {
-                        u64 m = w0 + L < AW ? cand_word(v, w0 + L) : 0ull;
-                        const int pc = __popcll(m);
-                        const int inc = wave_incl_scan(pc);
-                        int o = run + inc - pc;
-                        while (m) {
-                            C[o++] = (w0 + L) * 64 + __builtin_ctzll(m);
-                            m &= m - 1;
-                        }
-                        run += __shfl(inc, WAVE - 1, WAVE);
-                    }
-                }
-                __syncthreads();
-                nheavy = sTook;
-                hsel ^= 1;
-                if (L == 0 && work) atomicAdd(&q.ctl->hpairs, work);
+                for (int j = t; j < nheavy; j += BT)
+                    q.front[par][sAt + j] = CtFront{gi, q.hlist[hsel][base + j]};
                 if (t == 0) atomicAdd(&q.ctl->hand, 1ull);
-                break;                               // the grid takes them
+                break;
             }
-            // every vertex of the round has been counted: it ends
+            // every vertex of the round has been counted: it ends, with the
+            // candidate list as the grid left it, if it was kept
             phase = CT_ROUND;
-            rescan = true;
+            rescan = kept < 0;
+            kept = -1;
         } else {
             if (n_alive == 0) {
                 phase = CT_DONE;
@@ -571,25 +912,46 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
                 phase = CT_STOPPED;
                 break;
             }
+            // with other graphs waiting for the grid, the long runs of light
+            // rounds are cut so that those do not wait for them one by one
+            if (b.G > 1 && (++turn & 15) == 0) {
+                if (t == 0) sYield = __hip_atomic_load(&q.ctl->nfront[par], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > 0;
+                __syncthreads();
+                const bool yield = sYield != 0;
+                __syncthreads();
+                if (yield) break;
+            }
             // ---- the level: smallest candidate degree
             int32_t cid[CPT];
             u64 cd[CPT];
             u64 gmin = ~0ull;
+            int nj = 0;                              // candidates of a thread
             if (!rescan) {
                 const int nc = min(sN[cb], CC);
                 if (sN[cb] > CC) rescan = true;      // (uniform: every thread reads the same count)
+                nj = (nc + BT - 1) / BT;
 #pragma unroll
                 for (int j = 0; j < CPT; j++) {
+                    if (j >= nj) break;
                     const int i = j * BT + t;
-                    cid[j] = i < nc ? sCand[cb][i] : -1;
-                    cd[j] = cid[j] >= 0 ? ct_load_deg(&ldeg[cid[j]]) : ~0ull;
+                    cid[j] = sCand[cb][min(i, nc - 1)];
+                    cd[j] = ct_load_deg(&ldeg[cid[j]]);
+                    if (i >= nc) {
+                        cid[j] = -1;
+                        cd[j] = ~0ull;
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < CPT; j++) {
+                    if (j >= nj) break;
                     gmin = cd[j] < gmin ? cd[j] : gmin;
                 }
-                gmin = wave_min(gmin);
+                gmin = ct_wave_min(gmin);
                 if (L == 0) sMin[wv] = gmin;
-                __syncthreads();
+                ct_sync();
+                gmin = sMin[0];
 #pragma unroll
-                for (int j = 0; j < NW; j++) gmin = sMin[j] < gmin ? sMin[j] : gmin;
+                for (int j = 1; j < NW; j++) gmin = sMin[j] < gmin ? sMin[j] : gmin;
                 if (gmin == ~0ull) rescan = true;    // the list ran dry
             }
             bool mass = false;
@@ -597,27 +959,35 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
                 // a new threshold: the smallest degree, then the largest bin
                 // edge below which about half a list of vertices lies
                 __syncthreads();
-                uint32_t *hist = (uint32_t *)sS;     // (not in use between rounds)
-                for (int i = t; i < CT_BINS; i += BT) hist[i] = 0;
+                for (int i = t; i < CT_BINS; i += BT) sHist[i] = 0;
                 u64 m = ~0ull;
                 __syncthreads();
-                for (int l = t; l < A; l += BT) {
-                    if (!((sLive[l >> 6] >> (l & 63)) & 1ull)) continue;
-                    const u64 d = ct_load_deg(&ldeg[l]);
-                    m = d < m ? d : m;
-                    atomicAdd(&hist[ct_bin(d)], 1u);
+                for (int l0 = t; l0 < A; l0 += 8 * BT) {
+                    u64 d[8];
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        const int l = l0 + u * BT;
+                        d[u] = l < A && ((sLive[l >> 6] >> (l & 63)) & 1ull) ? ct_load_deg(&ldeg[l]) : ~0ull;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        if (d[u] == ~0ull) continue;   // (no degree: a count of 2^64 - 1 cliques is refused)
+                        m = d[u] < m ? d[u] : m;
+                        atomicAdd(&sHist[ct_bin(d[u])], 1u);
+                    }
                 }
-                m = wave_min(m);
+                m = ct_wave_min(m);
                 if (L == 0) sMin[wv] = m;
                 __syncthreads();
                 gmin = sMin[0];
+#pragma unroll
                 for (int j = 1; j < NW; j++) gmin = sMin[j] < gmin ? sMin[j] : gmin;
                 const u64 need = (!b.minpeel && k > gmin) ? k : gmin;
                 // every wave alike: a lane sums CT_BINS / WAVE bins
                 constexpr int BL = CT_BINS / WAVE;
                 uint32_t hs = 0, hb[BL];
 #pragma unroll
-                for (int i = 0; i < BL; i++) hs += hb[i] = hist[L * BL + i];
+                for (int i = 0; i < BL; i++) hs += hb[i] = sHist[L * BL + i];
                 uint32_t acc = wave_incl_scan(hs) - hs;
                 int bin = -1;
 #pragma unroll
@@ -634,20 +1004,29 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
                 }
                 cb = 0;
                 __syncthreads();
-                for (int l = t; l < A; l += BT) {
-                    if (!((sLive[l >> 6] >> (l & 63)) & 1ull)) continue;
-                    const u64 d = ct_load_deg(&ldeg[l]);
-                    if (d > T) continue;
-                    const int pos = atomicAdd(&sN[0], 1);
-                    if (pos < CC) sCand[0][pos] = l;
+                for (int l0 = t; l0 < A; l0 += 8 * BT) {
+                    u64 d[8];
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        const int l = l0 + u * BT;
+                        d[u] = l < A && ((sLive[l >> 6] >> (l & 63)) & 1ull) ? ct_load_deg(&ldeg[l]) : ~0ull;
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; u++) {
+                        if (d[u] == ~0ull || d[u] > T) continue;
+                        const int pos = atomicAdd(&sN[0], 1);
+                        if (pos < CC) sCand[0][pos] = l0 + u * BT;
+                    }
                 }
                 __syncthreads();
                 const int nc = sN[0];
                 mass = nc > CC;
                 rescan = mass;
                 if (!mass) {
+                    nj = (nc + BT - 1) / BT;
 #pragma unroll
                     for (int j = 0; j < CPT; j++) {
+                        if (j >= nj) break;
                         const int i = j * BT + t;
                         cid[j] = i < nc ? sCand[0][i] : -1;
                         cd[j] = cid[j] >= 0 ? ct_load_deg(&ldeg[cid[j]]) : ~0ull;
@@ -675,27 +1054,27 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
                     const u64 d = ct_load_deg(&ldeg[l]);
                     if (d > k) continue;
                     atomicOr((unsigned long long *)&sCur[l >> 6], 1ull << (l & 63));
-                    const int32_t v = q.glob[base + l];
-                    b.core[v] = label;
-                    b.stamp[v] = -1;
+                    ldeg[l] = label;                 // a removed vertex's slot: its core number (or round)
                     atomicAdd(&sNF[p], 1);
                     if (d) hl[atomicAdd(&sNH[p], 1)] = l;
                 }
                 __syncthreads();
                 nF = sNF[p];
-                nheavy = sNH[p];
+                nheavy = nF == n_alive ? 0 : sNH[p];   // (every alive vertex leaves: nothing to count)
                 dest = 0;
                 if (t == 0) {
-                    sNF[p ^ 1] = sNfl[p ^ 1] = sNH[p ^ 1] = sMaxD[p ^ 1] = 0;
+                    sNF[p ^ 1] = sNfl[p ^ 1] = sNH[p ^ 1] = 0;
                     sDest[p ^ 1] = sPairs[p ^ 1] = 0;
                 }
                 phase = CT_HEAVY;
+                fresh = false;
                 __syncthreads();
                 continue;
             }
             // ---- the frontier; the other candidates move to the next list
 #pragma unroll
             for (int j = 0; j < CPT; j++) {
+                if (j >= nj) break;
                 const bool have = cid[j] >= 0, take = have && cd[j] <= k;
                 const bool keep = have && !take, wk = take && cd[j] != 0;
                 const u64 mk = __ballot(keep), mt = __ballot(take), mw = __ballot(wk);
@@ -712,158 +1091,224 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
                 if (take) {
                     const int32_t l = cid[j];
                     atomicOr((unsigned long long *)&sCur[l >> 6], 1ull << (l & 63));
-                    const int32_t v = q.glob[base + l];
-                    b.core[v] = label;
-                    b.stamp[v] = -1;
+                    ldeg[l] = label;                 // a removed vertex's slot: its core number (or round)
                 }
             }
-            __syncthreads();
+            if (t == 0) sNext = 0;
+            ct_sync();
             nF = sNF[p];
-            const int nf = sNfl[p];
+            // every alive vertex leaves: no survivor's degree can fall, nothing to count
+            const int nf = nF == n_alive ? 0 : sNfl[p];
             if (t == 0) {
                 // the other parity's counters, read before this round's first barrier
-                sNF[p ^ 1] = sNfl[p ^ 1] = sNH[p ^ 1] = sMaxD[p ^ 1] = 0;
+                sNF[p ^ 1] = sNfl[p ^ 1] = sNH[p ^ 1] = 0;
                 sDest[p ^ 1] = sPairs[p ^ 1] = 0;
             }
-            // every alive vertex leaves: no survivor's degree can fall, nothing to count
-            const int nfw = nF == n_alive ? 0 : nf;
-            // ---- a wave per frontier vertex: count C_v, and at most 64 members at once
-            for (int f = wv; f < nfw; f += NW) {
-                const int32_t v = sF[f];
-                int c = 0;
-                for (int w = L; w < AW; w += WAVE) c += __popcll(cand_word(v, w));
-                const int d = wave_sum(c);
-                if (d < R) continue;
-                if (d > 64) {
-                    if (L == 0) {
-                        q.hlist[hsel][base + atomicAdd(&sNH[p], 1)] = v;
-                        atomicAdd(&sPairs[p], (u64)d * (u64)d);
-                        atomicMax(&sMaxD[p], d);
-                    }
-                    continue;
-                }
-                int run = 0;
-                for (int w0 = 0; w0 < AW; w0 += WAVE) {
-                    u64 m = w0 + L < AW ? cand_word(v, w0 + L) : 0ull;
-                    if (__ballot(m != 0) == 0) continue;
-                    const int pc = __popcll(m);
-                    const int inc = wave_incl_scan(pc);
-                    int o = run + inc - pc;
-                    while (m) {
-                        sWC[wv][o++] = (w0 + L) * 64 + __builtin_ctzll(m);
-                        m &= m - 1;
-                    }
-                    run += __shfl(inc, WAVE - 1, WAVE);
-                }
-                __builtin_amdgcn_wave_barrier();
-                const int32_t x = L < d ? sWC[wv][L] : 0;
-                const uint32_t *M32 = (const uint32_t *)M;
-                u64 row = 0;
-                for (int i0 = 0; i0 < d; i0 += 8) {
-                    uint32_t vv[8];
-#pragma unroll
-                    for (int u = 0; u < 8; u++) {
-                        const int32_t xi = __builtin_amdgcn_readlane(x, (i0 + u) & 63);
-                        vv[u] = (i0 + u < d && L < d) ? M32[(int64_t)xi * AW * 2 + (x >> 5)] : 0u;
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; u++) {
-                        const u64 bw = __ballot(L < d && ((vv[u] >> (x & 31)) & 1u));
-                        if (L == i0 + u) row = bw;
-                    }
-                }
-                sWS[wv][L] = row;
-                __builtin_amdgcn_wave_barrier();
-                u64 cx = 0;
-                if (L < d) {
-                    const u64 m1[1] = {row};
-                    cx = ct_count_in<R - 1, 1>(m1, sWS[wv], 1);
-                }
-                if (cx) apply(x, cx);
-                const u64 tot = wave_sum(cx);
-                if (L == 0) {
-                    if (tot) atomicAdd(&sDest[p], tot);
-                    work += (u64)d * (u64)d;
-                }
-                __builtin_amdgcn_wave_barrier();
+            if (nf > CT_FRONT) {
+                for (int j = t; j < nf; j += BT) q.hlist[hsel][base + j] = sF[j];
+                nheavy = nf;
+                dest = 0;
+                phase = CT_HEAVY;
+                fresh = true;
+                __syncthreads();
+                continue;
             }
-            __syncthreads();
-            dest = 0;
-            const int nh = sNH[p];
-            if (nh > 0) {
-                if (sMaxD[p] > DC || sPairs[p] > q.light) {
-                    nheavy = nh;
-                    dest = sDest[p];
-                    phase = CT_HEAVY;
-                    continue;                        // (the barrier above ordered hlist)
-                }
-                // ---- larger C_v one after another, the whole workgroup on each
-                for (int f = 0; f < nh; f++) {
-                    const int32_t v = q.hlist[hsel][base + f];
-                    const int per = (AW + BT - 1) / BT, w0 = min(AW, t * per), w1 = min(AW, w0 + per);
-                    int c = 0;
-                    for (int w = w0; w < w1; w++) c += __popcll(cand_word(v, w));
-                    const int inc = wave_incl_scan(c);
-                    if (L == WAVE - 1) sWsum[wv] = inc;
-                    __syncthreads();
-                    int o = inc - c, d = 0;
-                    for (int j = 0; j < NW; j++) {
-                        if (j < wv) o += sWsum[j];
-                        d += sWsum[j];
+            // ---- batches of frontier vertices: list the members, compact the
+            // rows, count, take the losses off the degrees
+            int32_t hold = -1;                       // this wave's vertex that found no room in the last batch
+            for (int bp = 0; nf > 0; bp ^= 1) {
+                // a wave per vertex
+                while (true) {
+                    int32_t v = hold;
+                    if (v < 0) {
+                        int f = 0;
+                        if (L == 0) f = atomicAdd(&sNext, 1);
+                        f = __builtin_amdgcn_readfirstlane(f);
+                        if (f >= nf) break;
+                        v = sF[f];
                     }
-                    for (int w = w0; w < w1; w++) {
-                        u64 m = cand_word(v, w);
+                    hold = -1;
+                    constexpr int WR = 4;            // row words a lane keeps (rows of at most 256 words)
+                    u64 wr[WR];
+                    int c = 0;
+#pragma unroll
+                    for (int u = 0; u < WR; u++) wr[u] = M[(int64_t)v * AW + min(u * WAVE + L, AW - 1)];
+#pragma unroll
+                    for (int u = 0; u < WR; u++) {
+                        const int w = min(u * WAVE + L, AW - 1);
+                        wr[u] = ct_cand(wr[u], sLive[w], sCur[w], v, w);
+                        if (u * WAVE + L >= AW) wr[u] = 0;
+                        c += __popcll(wr[u]);
+                    }
+                    for (int w = WR * WAVE + L; w < AW; w += WAVE)
+                        c += __popcll(ct_cand(M[(int64_t)v * AW + w], sLive[w], sCur[w], v, w));
+                    const int d = ct_wave_sum(c);
+                    if (d < R) continue;
+                    int vi = 0, m0 = 0, r0 = 0;
+                    const int st = ct_lds_stride(ct_lds_words(d));
+                    if (L == 0) {
+                        const u64 dd = (u64)d * (u64)d;
+                        const u64 pairs = (u64)d * (u64)AW + dd / 4 + (R > 3 ? dd * (u64)d / 64 : 0);
+                        if (d > DC || atomicAdd(&sPairs[p], pairs) + pairs > CT_LIGHT) {
+                            q.hlist[hsel][base + atomicAdd(&sNH[p], 1)] = v;
+                            vi = -2;                 // the grid takes it
+                        } else {
+                            const u64 old = atomicAdd(&sAlloc[bp], (1ull << 48) | ((u64)d << 24) | (u64)(d * st));
+                            vi = (int)(old >> 48);
+                            m0 = (int)(old >> 24) & 0xffffff;
+                            r0 = (int)(old & 0xffffff);
+                            if (vi >= CT_VS || m0 + d > SLOTS || r0 + d * st > ROWW) {
+                                atomicAdd(&sPairs[p], (u64)0 - pairs);
+                                vi = -1;             // the next batch
+                            } else {
+                                sVm[vi] = m0;
+                                sVd[vi] = d;
+                                sVr[vi] = r0;
+                                atomicMax(&sSlots[bp], m0 + d);
+                                atomicMax(&sNv[bp], vi + 1);
+                                work += dd;
+                            }
+                        }
+                    }
+                    vi = __builtin_amdgcn_readfirstlane(vi);
+                    m0 = __builtin_amdgcn_readfirstlane(m0);
+                    if (vi == -2) continue;
+                    if (vi == -1) {
+                        hold = v;
+                        if (L == 0) atomicAdd(&sPend[bp], 1);
+                        break;
+                    }
+                    int run = m0;
+#pragma unroll
+                    for (int u = 0; u < WR; u++) {
+                        if (u * WAVE >= AW) break;
+                        const int pc = __popcll(wr[u]);
+                        int o = run + ct_wave_prefix(pc);
+                        u64 m = wr[u];
                         while (m) {
-                            sC[o++] = w * 64 + __builtin_ctzll(m);
+                            sId[o] = (u * WAVE + L) * 64 + __builtin_ctzll(m);
+                            sCnt[o] = 0;
+                            o++;
                             m &= m - 1;
                         }
+                        run += ct_wave_sum(pc);
                     }
-                    __syncthreads();
-                    const int W = (d + 63) >> 6;
-                    const uint32_t *M32 = (const uint32_t *)M;
-                    for (int i = wv; i < d; i += NW) {
-                        const uint32_t *Mx = M32 + (int64_t)sC[i] * AW * 2;
-                        uint32_t vv[DW];
-                        int32_t cj[DW];
-#pragma unroll
-                        for (int u = 0; u < DW; u++) {
-                            const int j = u * 64 + L;
-                            cj[u] = j < d ? sC[j] : -1;
-                            vv[u] = cj[u] >= 0 ? Mx[cj[u] >> 5] : 0u;
+                    for (int w0 = WR * WAVE; w0 < AW; w0 += WAVE) {
+                        const int w = w0 + L;
+                        u64 m = w < AW ? ct_cand(M[(int64_t)v * AW + w], sLive[w], sCur[w], v, w) : 0ull;
+                        const int pc = __popcll(m);
+                        int o = run + ct_wave_prefix(pc);
+                        while (m) {
+                            sId[o] = w * 64 + __builtin_ctzll(m);
+                            sCnt[o] = 0;
+                            o++;
+                            m &= m - 1;
                         }
-                        u64 mine = 0;
-#pragma unroll
-                        for (int u = 0; u < DW; u++) {
-                            const u64 bw = __ballot(cj[u] >= 0 && ((vv[u] >> (cj[u] & 31)) & 1u));
-                            if (L == u) mine = bw;
-                        }
-                        if (L < DW) sS[i * DS + L] = mine;
-                    }
-                    __syncthreads();
-                    u64 mydest = 0;
-                    for (int i = wv; i < d; i += NW) {
-                        u64 cx;
-                        if (W <= 2) cx = ct_member_small<R, 2>(i, d, sS, DS);
-                        else if (W <= 4) cx = ct_member_small<R, 4>(i, d, sS, DS);
-                        else cx = ct_member_small<R, (DW < 4 ? 4 : DW)>(i, d, sS, DS);
-                        if (L == 0) {
-                            sCnt[i] = cx;
-                            mydest += cx;
-                        }
-                    }
-                    if (L == 0) {
-                        if (mydest) atomicAdd(&sDest[p], mydest);
-                        if (wv == 0) work += (u64)d * (u64)d;
-                    }
-                    __syncthreads();
-                    for (int i = t; i < d; i += BT) {
-                        const u64 cx = sCnt[i];
-                        if (cx) apply(sC[i], cx);
+                        run += ct_wave_sum(pc);
                     }
                 }
-                __syncthreads();
+                ct_sync();
+                const int slots = sSlots[bp], nv = sNv[bp];
+                const bool more = sPend[bp] > 0;
+                if (t == 0) {                        // the next batch's counters
+                    sAlloc[bp ^ 1] = 0;
+                    sSlots[bp ^ 1] = 0;
+                    sNv[bp ^ 1] = 0;
+                    sPend[bp ^ 1] = 0;
+                }
+                ct_rows<WB, NW>(batch, nv, M, AW, sRow[wv]);
+                ct_sync();
+                // count
+                {
+                    const int lm = sVm[L], ld = sVd[L], lr = sVr[L];
+                    int turn = wv;
+                    for (int vi = 0; vi < nv; vi++) {
+                        const int m0 = __builtin_amdgcn_readlane(lm, vi), d = __builtin_amdgcn_readlane(ld, vi);
+                        const int Wt = ct_lds_words(d), st = ct_lds_stride(Wt);
+                        const u64 *S = sS + __builtin_amdgcn_readlane(lr, vi);
+                        u64 *cn = sCnt + m0;
+                        if constexpr (R == 3) {
+                            int units;
+                            if (d <= 64) {
+                                constexpr int MB = 8;
+                                units = (d + MB - 1) / MB;
+                                for (int g = turn; g < units; g += NW)
+                                    ct_member_tri<1, MB>(g * MB, min(MB, d - g * MB), d, S, st, cn);
+                            } else {
+                                units = (d + 31) / 32;
+                                for (int g = turn; g < units; g += NW) {
+                                    if (d <= 128) ct_tri_block<4>(g, d, S, st, cn);
+                                    else if (DC <= 256 || d <= 256) ct_tri_block<8>(g, d, S, st, cn);
+                                    else ct_tri_block<(DC <= 256 ? 8 : 16)>(g, d, S, st, cn);
+                                }
+                            }
+                            turn = (turn - units) & (NW - 1);
+                        } else {
+                            // the wave gathers the edges of its members in a queue, a lane takes an edge
+                            int qn = 0;
+                            uint32_t *qu = sQ[wv];
+                            auto drain = [&](int take) {
+                                if (Wt == 1) ct_edge_drain<R, 1>(qu, take, S, st, cn);
+                                else if (Wt == 2) ct_edge_drain<R, 2>(qu, take, S, st, cn);
+                                else ct_edge_drain<R, 4>(qu, take, S, st, cn);
+                            };
+                            for (int i = turn; i < d; i += NW) {
+                                const u64 mine = S[i * st + (L < Wt ? L : 0)];
+                                for (int w = i >> 6; w < Wt; w++) {
+                                    const u64 m = bcast64(mine, w) & ct_above(w, i);
+                                    if (!m) continue;
+                                    if ((m >> L) & 1ull)
+                                        qu[qn + __popcll(m & lanemask_lt())] =
+                                            ((uint32_t)i << 16) | (uint32_t)(w * 64 + L);
+                                    qn += __popcll(m);
+                                    __builtin_amdgcn_wave_barrier();
+                                    if (qn >= WAVE) {
+                                        drain(WAVE);
+                                        const int rest = qn - WAVE;
+                                        uint32_t keep = 0;
+                                        if (L < rest) keep = qu[WAVE + L];
+                                        __builtin_amdgcn_wave_barrier();
+                                        if (L < rest) qu[L] = keep;
+                                        qn = rest;
+                                        __builtin_amdgcn_wave_barrier();
+                                    }
+                                }
+                            }
+                            if (qn) drain(qn);
+                            turn = (turn - d) & (NW - 1);
+                        }
+                    }
+                }
+                ct_sync();
+                for (int sl = t; sl < slots; sl += BT) {
+                    const u64 c = sCnt[sl] / (u64)(R == 3 ? 2 : (R - 1) * (R - 2) / 2);
+                    if (!c) continue;
+                    const int32_t x = sId[sl];
+                    atomicAdd(&sDest[p], c);
+                    if ((sCur[x >> 6] >> (x & 63)) & 1ull) continue;   // leaves in this round
+                    const u64 old = ct_sub_deg(&ldeg[x], c);
+                    if (old > T && old - c <= T) {
+                        const int pos = atomicAdd(&sN[cb ^ 1], 1);
+                        if (pos < CC) sCand[cb ^ 1][pos] = x;
+                    }
+                }
+                ct_sync();
+                if (!more) break;
+            }
+            if (t == 0) {                            // the next round's first batch
+                sAlloc[0] = sAlloc[1] = 0;
+                sSlots[0] = sSlots[1] = 0;
+                sNv[0] = sNv[1] = 0;
+                sPend[0] = sPend[1] = 0;
             }
             dest = sDest[p];
+            if (sNH[p] > 0) {
+                nheavy = sNH[p];
+                phase = CT_HEAVY;
+                fresh = true;
+                __syncthreads();                     // orders hlist
+                continue;
+            }
             cb ^= 1;
         }
         // ---- the end of the round
@@ -874,26 +1319,16 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
         rounds += 1;
         open = false;
         dest = 0;
-        if (rescan) {
-            // a round that marked or changed many: clear the frontier everywhere
-            __syncthreads();
-            for (int w = t; w < AW; w += BT) {
-                sLive[w] &= ~sCur[w];
+        if (rescan) __syncthreads();
+        for (int w = t; w < AW; w += BT) {
+            const u64 m = sCur[w];
+            if (m) {
+                sLive[w] &= ~m;
                 sCur[w] = 0;
             }
-            __syncthreads();
-        } else {
-            // few frontier vertices: each thread still holds its own (in the
-            // words it marked); the words are cleared whole by their first owner
-            for (int w = t; w < AW; w += BT) {
-                const u64 m = sCur[w];
-                if (m) {
-                    sLive[w] &= ~m;
-                    sCur[w] = 0;
-                }
-            }
-            if (t == 0) sN[cb ^ 1] = 0;              // the list just consumed becomes the next round's target
         }
+        if (rescan) __syncthreads();
+        else if (t == 0) sN[cb ^ 1] = 0;             // the list just consumed becomes the next round's target
     }
     __syncthreads();
     // the state, for the next launch
@@ -901,10 +1336,18 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
         q.lb[cg.boff + w] = sLive[w];
         q.cb[cg.boff + w] = sCur[w];
     }
-    if (phase == CT_STOPPED)
-        for (int l = t; l < A; l += BT)
-            if ((sLive[l >> 6] >> (l & 63)) & 1ull) b.deg[q.glob[base + l]] = ct_load_deg(&ldeg[l]);
-    if (phase != CT_HEAVY && L == 0 && work) atomicAdd(&q.ctl->pairs, work);
+    if (phase >= CT_DONE)
+        for (int l = t; l < A; l += BT) {
+            const int32_t v = q.glob[base + l];
+            const u64 x = ct_load_deg(&ldeg[l]);
+            if ((sLive[l >> 6] >> (l & 63)) & 1ull) {
+                b.deg[v] = x;                        // (only when stopped)
+            } else {
+                b.core[v] = x;
+                b.stamp[v] = -1;
+            }
+        }
+    if (L == 0 && work) atomicAdd(&q.ctl->pairs, work);
     if (t == 0) {
         cg.k = k;
         cg.mu = mu;
@@ -914,9 +1357,11 @@ __global__ __launch_bounds__(BT) void k_ct_engine(PeelBufs b, CtBufs q, const in
         cg.rounds = rounds;
         cg.open = open ? 1 : 0;
         cg.phase = phase;
-        cg.nheavy = nheavy;
+        cg.nheavy = 0;                               // (the grid counts those it finds no room for)
         cg.hsel = hsel;
         cg.dest = dest;
+        cg.T = T;
+        cg.ncand = kept;
         if (phase >= CT_DONE) {
             GraphState &g = b.gs[cg.g];
             g.k = k;
@@ -1007,9 +1452,16 @@ __global__ void k_ct_close(PeelCtl *c, int32_t left) {
 
 template <int R>
 void ct_sequence(const PeelBufs &b, const CtBufs &q, const int32_t *small, int nsmall, const int32_t *large, int nlarge,
+                 int64_t widest,
                  int par, int64_t shrink_at, hipStream_t s) {
-    if (nsmall) k_ct_engine<256, 1024, 256, (int)CT_SMALL, R><<<nsmall, 256, 0, s>>>(b, q, small, par, 0);
-    if (nlarge) k_ct_engine<1024, 2048, 512, (int)CT_MAX, R><<<nlarge, 1024, 0, s>>>(b, q, large, par, shrink_at);
+    if (nsmall)
+        k_ct_engine<1024, 512, 2560, (int)CT_SMALL, (int)CT_SMALL / 64, R><<<nsmall, CT_BLOCK, 0, s>>>(b, q, small, par, 0);
+    if (nlarge && widest <= CT_MID)
+        k_ct_engine<2048, 1024, 5120, (int)CT_MID, (int)CT_MID / 64, R><<<nlarge, CT_BLOCK, 0, s>>>(b, q, large, par,
+                                                                                                 shrink_at);
+    else if (nlarge)
+        k_ct_engine<2048, 1024, 5120, (int)CT_MAX, 0, R><<<nlarge, CT_BLOCK, 0, s>>>(b, q, large, par, shrink_at);
+    k_ct_front<<<512, BLOCK, 0, s>>>(q, par);
     k_ct_edges<<<1024, BLOCK, 0, s>>>(q, par);
     k_ct_count<R><<<1024, BLOCK, 0, s>>>(q, par);
     DSD_HIP(hipGetLastError());
@@ -1065,15 +1517,13 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
         const int64_t acap = std::max<int64_t>(one, std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
         if (first) {
             size_t free_b = 0, total_b = 0;
-            const size_t need = 8 * (size_t)(words + acap + 2 * sets) + 96 * (size_t)total;
+            const size_t need = 8 * (size_t)(words + acap + 2 * sets) + 112 * (size_t)total;
             if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4) return false;
         }
         first = false;
         CtBufs q{};
         q.R = R;
         q.minpeel = b.minpeel;
-        // with many graphs the other CUs have work of their own
-        q.light = cg.size() >= 32 ? ~0ull : CT_LIGHT_PAIRS;
         q.acap = acap;
         q.ctl = sc.get_n<CtCtl>(1);
         q.cg = sc.get_n<CtGraph>((int64_t)cg.size());
@@ -1086,6 +1536,9 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
         q.hlist[1] = sc.get_n<int32_t>(total);
         q.items[0] = sc.get_n<CtItem>(total);
         q.items[1] = sc.get_n<CtItem>(total);
+        q.cand = sc.get_n<int32_t>(total);
+        q.front[0] = sc.get_n<CtFront>(total);
+        q.front[1] = sc.get_n<CtFront>(total);
         q.arena = sc.get_n<u64>(acap);
         uint32_t *flag = sc.get_n<uint32_t>(b.n), *loc = sc.get_n<uint32_t>(b.n);
         int32_t *lists = sc.get_n<int32_t>((int64_t)cg.size());
@@ -1117,9 +1570,9 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
         while (true) {
             for (int i = 0; i < chunk; i++, par ^= 1) {
                 switch (R) {
-                    case 3: ct_sequence<3>(b, q, lists, nsmall, lists + nsmall, nlarge, par, shrink_at, s); break;
-                    case 4: ct_sequence<4>(b, q, lists, nsmall, lists + nsmall, nlarge, par, shrink_at, s); break;
-                    case 5: ct_sequence<5>(b, q, lists, nsmall, lists + nsmall, nlarge, par, shrink_at, s); break;
+                    case 3: ct_sequence<3>(b, q, lists, nsmall, lists + nsmall, nlarge, widest, par, shrink_at, s); break;
+                    case 4: ct_sequence<4>(b, q, lists, nsmall, lists + nsmall, nlarge, widest, par, shrink_at, s); break;
+                    case 5: ct_sequence<5>(b, q, lists, nsmall, lists + nsmall, nlarge, widest, par, shrink_at, s); break;
                     default: throw Error(-1, "h outside [4, 6]");
                 }
             }
