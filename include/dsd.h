@@ -193,7 +193,8 @@ dsd_status dsd_clique_degrees_noalloc(dsd_graph g, int h, int out_mem, uint64_t 
  * library's kernels, not a step of the method).  The enumeration bins DAG
  * roots into classes by out-degree, one launch each: h >= 4: class 0 up to
  * 64 (a wave per root), 1 up to 256, 2 up to 768, 3 up to 1,280 and 4 up to
- * 2,048 (workgroups with bitmaps in LDS for 1-2, in global memory for 3-4);
+ * 2,048 (workgroups with bitmaps in LDS for 1-2, h = 4 also up to 1,088
+ * out-neighbours, in global memory beyond; a class may be two launches);
  * h = 3: class 0 up to 64, 1 up to 2,048, 2 larger.  Each launch's grid is
  * capped (workgroups loop over the class's roots).
  *

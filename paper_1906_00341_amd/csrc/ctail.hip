@@ -626,47 +626,6 @@ __device__ __forceinline__ void ct_member_tri(int i0, int n, int d, const u64 *S
     if (L < n) cnt[i0 + L] = (u64)(uint32_t)tot;
 }
 
-// The same for a vertex of more than 64 members: row sums of A o A^2 (A its
-// members' 0/1 adjacency), a contraction, on the matrix cores.  A unit is a
-// column block J of 32 members: C = A[I] A[J]^T by 32 x 32 x 32 products of
-// bytes for every row block I, then every lane adds its column's entries
-// where A holds a 1.  Bits become bytes by a multiplication (four at a time);
-// A is symmetric, so both operands read rows, and the order of the k index
-// does not matter as long as it is the same for both.  Rows past the last
-// member repeat it; their products meet zero bits only.
-// d = 256: popcounts (four words a pair, lanes half idle) 62,000 cycles on one CU, these products 10,000.
-typedef int ct_i4 __attribute__((ext_vector_type(4)));
-typedef int ct_i16 __attribute__((ext_vector_type(16)));
-__device__ __forceinline__ ct_i4 ct_bytes(uint32_t bits) {
-    ct_i4 v;
-#pragma unroll
-    for (int u = 0; u < 4; u++) v[u] = (int)((((bits >> (4 * u)) & 15u) * 0x00204081u) & 0x01010101u);
-    return v;
-}
-template <int TMAX>
-__device__ __forceinline__ void ct_tri_block(int J, int d, const u64 *S, int st, u64 *cnt) {
-    const int L = lane(), lo = L & 31, sh = (L >> 5) * 16;
-    const uint32_t *S32 = (const uint32_t *)S;
-    const int T = (d + 31) >> 5;
-    const int j = J * 32 + lo, jr = min(j, d - 1) * 2 * st;
-    ct_i4 bj[TMAX];
-#pragma unroll
-    for (int k = 0; k < TMAX; k++)
-        if (k < T) bj[k] = ct_bytes(S32[jr + k] >> sh);
-    uint32_t sum = 0;
-    for (int I = 0; I < T; I++) {
-        const int ir = min(I * 32 + lo, d - 1) * 2 * st;
-        const uint32_t mask = S32[jr + I] >> (4 * (L >> 5));   // register r holds row 8 (r / 4) + 4 (lane / 32) + r % 4
-        ct_i16 acc = {};
-#pragma unroll
-        for (int k = 0; k < TMAX; k++)
-            if (k < T) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(ct_bytes(S32[ir + k] >> sh), bj[k], acc, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 16; r++) sum += (uint32_t)acc[r] & (0u - ((mask >> (8 * (r / 4) + r % 4)) & 1u));
-    }
-    if (j < d && sum) atomicAdd(&cnt[j], (u64)sum);
-}
-
 // words of a member's compact row in LDS, and their stride: odd beyond one
 // word, so that the lanes' rows spread over the banks
 __device__ __forceinline__ int ct_lds_words(int d) {
@@ -1229,6 +1188,8 @@ __global__ __launch_bounds__(CT_BLOCK) void k_ct_engine(PeelBufs b, CtBufs q, co
                         u64 *cn = sCnt + m0;
                         if constexpr (R == 3) {
                             int units;
+                            // beyond 64 members on the matrix cores (d = 256: popcounts 62,000 cycles
+                            // on one CU, products 10,000)
                             if (d <= 64) {
                                 constexpr int MB = 8;
                                 units = (d + MB - 1) / MB;
@@ -1237,9 +1198,9 @@ __global__ __launch_bounds__(CT_BLOCK) void k_ct_engine(PeelBufs b, CtBufs q, co
                             } else {
                                 units = (d + 31) / 32;
                                 for (int g = turn; g < units; g += NW) {
-                                    if (d <= 128) ct_tri_block<4>(g, d, S, st, cn);
-                                    else if (DC <= 256 || d <= 256) ct_tri_block<8>(g, d, S, st, cn);
-                                    else ct_tri_block<(DC <= 256 ? 8 : 16)>(g, d, S, st, cn);
+                                    if (d <= 128) tri_block<4>(g, d, S, st, cn);
+                                    else if (DC <= 256 || d <= 256) tri_block<8>(g, d, S, st, cn);
+                                    else tri_block<(DC <= 256 ? 8 : 16)>(g, d, S, st, cn);
                                 }
                             }
                             turn = (turn - units) & (NW - 1);

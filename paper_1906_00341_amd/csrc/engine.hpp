@@ -17,7 +17,9 @@
 //        = rank order, so "out" = higher index).  Members in prefix positions
 //        get their counts from popcounts of intersected rows; the last member
 //        y of a clique gets, in one pass, the number of (R-1)-cliques inside
-//        its in-neighbourhood Col(y).  No work is done per clique.
+//        its in-neighbourhood Col(y).  No work is done per clique.  (The row
+//        engine, R = 3 and 4 up to 1,088 and 768 members: the matrix cores
+//        and a walk over triangles instead.)
 //
 // Context interface (Ctx):
 //   int32_t root(int64_t item)                 -- w
@@ -140,6 +142,103 @@ __device__ u64 bitmap_node_work(int x, const u64 *S, u64 *cnt) {
     c += count_in<R - 1, W>(M, S);
     if (c) atomicAdd(&cnt[x], c);
     return tot;
+}
+
+// ---------------------------------------------------------------- counts over LDS bitmaps
+
+// Row sums of A o A^2 on the matrix cores: for every member j of a candidate
+// set (0/1 adjacency A, rows S of stride st words, symmetric, zero bits past
+// member d - 1), twice the triangles that hold j.  A unit is a column block J
+// of 32 members: C = A[I] A[J]^T by 32 x 32 x 32 products of bytes for every
+// row block I, then every lane adds its column's entries where A holds a 1.
+// A byte comes from a bit by one AND: operand A keeps bit s of every byte at
+// its place (value 2^s, s = 0..3, the other half wave's bits 4..7 shifted
+// down), operand B moves it to place 3 - s, so that every product is 8.  A is
+// symmetric, so both operands read rows, and the order of the k index does not
+// matter as long as both take the same.  Rows past the last member repeat it;
+// their products meet zero bits only.  Bound by the matrix cores (32 cycles a
+// product, five vector operations beside it).
+typedef int tri_i4 __attribute__((ext_vector_type(4)));
+typedef int tri_i16 __attribute__((ext_vector_type(16)));
+template <int TMAX, class Cnt>
+__device__ __forceinline__ void tri_block(int J, int d, const u64 *S, int st, Cnt *cnt) {
+    const int L = lane(), lo = L & 31, sh = (L >> 5) * 4;
+    const int T = (d + 31) >> 5;
+    const int j = J * 32 + lo, jr = min(j, d - 1) * st;
+    tri_i4 bj[TMAX];
+#pragma unroll
+    for (int k = 0; k < TMAX; k += 2) {
+        if (k < T) {
+            const u64 w = S[jr + (k >> 1)];
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const uint32_t x = (uint32_t)(w >> (32 * h)) >> sh;
+#pragma unroll
+                for (int s = 0; s < 4; s++) bj[k + h][s] = (int)(((x >> s) & 0x01010101u) << (3 - s));
+            }
+        }
+    }
+    uint32_t sum = 0;
+    for (int I = 0; I < T; I++) {
+        const int ir = min(I * 32 + lo, d - 1) * st;
+        // register r of the product holds row 8 (r / 4) + 4 (lane / 32) + r % 4
+        const uint32_t mask = (uint32_t)(S[jr + (I >> 1)] >> (32 * (I & 1))) >> sh;
+        tri_i16 acc = {};
+#pragma unroll
+        for (int k = 0; k < TMAX; k += 2) {
+            if (k < T) {
+                const u64 w = S[ir + (k >> 1)];
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    const uint32_t x = (uint32_t)(w >> (32 * h)) >> sh;
+                    tri_i4 a;
+#pragma unroll
+                    for (int s = 0; s < 4; s++) a[s] = (int)(x & (0x01010101u << s));
+                    acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, bj[k + h], acc, 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) sum += (uint32_t)acc[r] & (0u - ((mask >> (8 * (r / 4) + r % 4)) & 1u));
+    }
+    if (j < d && sum) atomicAdd(&cnt[j], (Cnt)(sum >> 3));
+}
+
+// R = 4: the edges (x, y), x < y, of the queue's codes (x << 16 | y), a lane
+// each: every triangle (x, y, z), z above y, gives its corners the number of
+// their common neighbours, so a member ends with three times its 4-cliques.
+template <int W>
+__device__ __forceinline__ void quad_drain(const uint32_t *qu, int take, const u64 *S, int st, u64 *cnt) {
+    const int L = lane();
+    if (L < take) {
+        const uint32_t code = qu[L];
+        const int x = (int)(code >> 16), y = (int)(code & 0xffffu);
+        const u64 *rx = S + x * st, *ry = S + y * st;
+        u64 M[W], sum = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) M[w] = rx[w] & ry[w];
+        for (int w = y >> 6; w < W; w++) {
+            u64 word = rx[w] & ry[w];                    // (from LDS: an index into M would leave the registers)
+            if (w == (y >> 6)) word &= (y & 63) == 63 ? 0ull : (~0ull << ((y & 63) + 1));
+            while (word) {
+                const int z = w * 64 + __builtin_ctzll(word);
+                word &= word - 1;
+                const u64 *rz = S + z * st;
+                uint32_t c = 0;
+#pragma unroll
+                for (int q = 0; q < W; q++) c += (uint32_t)__popcll(M[q] & rz[q]);
+                if (c) {
+                    atomicAdd(&cnt[z], (u64)c);
+                    sum += c;
+                }
+            }
+        }
+        if (sum) {
+            atomicAdd(&cnt[x], sum);
+            atomicAdd(&cnt[y], sum);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
 }
 
 // ---------------------------------------------------------------- LDS hash
@@ -401,6 +500,174 @@ __global__ __launch_bounds__(BLOCK) void k_engine_block(Ctx ctx, const int64_t *
             }
         }
         if (threadIdx.x == 0 && total) ctx.add_prefix(it, total);
+        __syncthreads();
+    }
+}
+
+// ---- row engine: one workgroup per item, a wave per member's out-list -------
+// R = 2, 3, 4; CAP: max |N+(w)|; SB: 2^SB hash slots; W: bitmap words a row
+// (R >= 3).  A wave walks N+(x) of one member x at a time, coalesced, four
+// entries a lane in flight, and probes the hash of C: no search for the
+// (member, entry) pair a lane holds, which took ten dependent LDS reads a
+// pair.  A slot holds 20 bits of the entry's hash beside its index, so most
+// misses end with one read.  R = 3 counts on the matrix cores (tri_block),
+// R = 4 by triangles (quad_drain), R = 2 by the hits themselves.  Clique-
+// degrees of R-MAT scale 22, h = 4 (2.9e10 probes): 400 -> 96 ms; of R-MAT
+// scale 18, h = 5: 139 -> 17 ms, against a search per pair, one thread per
+// member and 64-bit LDS atomics per prefix.
+template <int R, int CAP, int SB, int W, int BT, class Ctx>
+__global__ __launch_bounds__(BT) void k_engine_rows(Ctx ctx, const int64_t *row_ptr, const int32_t *col,
+                                                    const int64_t *dag_off, int64_t nitems) {
+    constexpr int NW = BT / WAVE, ST = W | 1;
+    __shared__ u64 sS[R >= 3 ? CAP * ST : 1];
+    __shared__ int32_t sC[CAP];
+    __shared__ uint32_t sH[1 << SB];
+    __shared__ u64 sCnt64[R >= 4 ? CAP : 1];
+    __shared__ uint32_t sQ[NW][R >= 4 ? 2 * WAVE : 1];
+    __shared__ int32_t sWsum[NW];
+    __shared__ u64 sTot[NW];
+    static_assert((1 << SB) >= CAP && CAP <= 2048, "indexes fit a slot, counters the table");
+    uint32_t *cnt = sH;                                // R = 3: the table's space, once it has been used
+    __shared__ uint32_t sCnt2[R == 2 ? CAP : 1];
+    const int t = threadIdx.x, wv = t / WAVE, L = lane();
+    for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
+        const int32_t w = ctx.root(it);
+        const int64_t s0 = dag_off[w];
+        const int d = (int)(row_ptr[w + 1] - s0);
+        for (int i = t; i < (1 << SB); i += BT) sH[i] = 0;
+        // candidates, rank order kept
+        int dd = 0;
+        for (int i0 = 0; i0 < d; i0 += BT) {
+            const int i = i0 + t;
+            const int32_t x = i < d ? col[s0 + i] : -1;
+            const bool ok = i < d && ctx.accept(it, x);
+            const u64 m = __ballot(ok);
+            if (L == 0) sWsum[wv] = __popcll(m);
+            __syncthreads();
+            int at = dd + __popcll(m & lanemask_lt());
+            for (int q = 0; q < NW; q++) {
+                if (q < wv) at += sWsum[q];
+                dd += sWsum[q];
+            }
+            if (ok) sC[at] = x;
+            __syncthreads();
+        }
+        if (dd < R) continue;                          // block-uniform
+        if constexpr (R >= 3)
+            for (int i = t; i < dd * ST; i += BT) sS[i] = 0;
+        for (int i = t; i < dd; i += BT) {
+            const uint32_t h = (uint32_t)sC[i] * 2654435761u, slot = 0x80000000u | ((h & 0xfffffu) << 11) | (uint32_t)i;
+            uint32_t at = h >> (32 - SB);
+            while (atomicCAS(&sH[at], 0u, slot) != 0u) at = (at + 1) & ((1u << SB) - 1u);
+            if constexpr (R == 2) sCnt2[i] = 0;
+            if constexpr (R >= 4) sCnt64[i] = 0;
+        }
+        __syncthreads();
+        u64 hits = 0;
+        for (int c0 = 0; c0 < dd; c0 += WAVE) {
+            // 64 members' out-lists: a lane holds one's start and length
+            const int32_t x = sC[min(c0 + L, dd - 1)];
+            const int64_t o0 = dag_off[x];
+            const int32_t ln = (int32_t)(row_ptr[x + 1] - o0);
+            for (int mi = wv; mi < WAVE && c0 + mi < dd; mi += NW) {
+                const int i = c0 + mi;
+                const int32_t len = __builtin_amdgcn_readlane(ln, mi);
+                const uint32_t plo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)o0, mi);
+                const uint32_t phi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((u64)o0 >> 32), mi);
+                const int32_t *list = col + (int64_t)(((u64)phi << 32) | plo);
+                uint32_t own = 0;
+                for (int e0 = 0; e0 < len; e0 += 4 * WAVE) {
+                    int32_t y[4];
+                    uint32_t h[4], sl[4];
+#pragma unroll
+                    for (int u = 0; u < 4; u++) y[u] = list[min(e0 + u * WAVE + L, len - 1)];
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        h[u] = (uint32_t)y[u] * 2654435761u;
+                        sl[u] = sH[h[u] >> (32 - SB)];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; u++) {
+                        if (e0 + u * WAVE >= len) break;
+                        uint32_t s = e0 + u * WAVE + L < len ? sl[u] : 0u, at = h[u] >> (32 - SB);
+                        const uint32_t tag = 0x100000u | (h[u] & 0xfffffu);
+                        int j = -1;
+                        while (s) {
+                            if ((s >> 11) == tag && sC[s & 0x7ffu] == y[u]) {
+                                j = (int)(s & 0x7ffu);
+                                break;
+                            }
+                            at = (at + 1) & ((1u << SB) - 1u);
+                            s = sH[at];
+                        }
+                        if (j >= 0) {
+                            if constexpr (R == 2) {
+                                atomicAdd(&sCnt2[j], 1u);
+                                own++;
+                            } else {
+                                atomicOr((unsigned long long *)&sS[i * ST + (j >> 6)], 1ull << (j & 63));
+                                atomicOr((unsigned long long *)&sS[j * ST + (i >> 6)], 1ull << (i & 63));
+                            }
+                        }
+                    }
+                }
+                if constexpr (R == 2) {
+                    own = wave_sum(own);
+                    hits += own;
+                    if (L == 0 && own) atomicAdd(&sCnt2[i], own);
+                }
+            }
+        }
+        __syncthreads();
+        u64 tot = 0;                                   // members' counts, each clique once for each of its R members
+        if constexpr (R == 3) {
+            for (int i = t; i < dd; i += BT) cnt[i] = 0;
+            __syncthreads();
+            for (int J = wv; J * 32 < dd; J += NW) tri_block<(CAP + 63) / 64 * 2>(J, dd, sS, ST, cnt);
+        } else if constexpr (R == 4) {
+            int qn = 0;
+            uint32_t *qu = sQ[wv];
+            for (int i = wv; i < dd; i += NW) {
+                const u64 mine = sS[i * ST + min(L, W - 1)];
+                for (int q = i >> 6; q < W; q++) {
+                    u64 m = __shfl(mine, q, WAVE);
+                    if (q == (i >> 6)) m &= (i & 63) == 63 ? 0ull : (~0ull << ((i & 63) + 1));
+                    if (!m) continue;                  // wave-uniform
+                    if ((m >> L) & 1ull) qu[qn + __popcll(m & lanemask_lt())] = ((uint32_t)i << 16) | (uint32_t)(q * 64 + L);
+                    qn += __popcll(m);
+                    __builtin_amdgcn_wave_barrier();
+                    if (qn >= WAVE) {
+                        quad_drain<W>(qu, WAVE, sS, ST, sCnt64);
+                        const int rest = qn - WAVE;
+                        uint32_t keep = 0;
+                        if (L < rest) keep = qu[WAVE + L];
+                        __builtin_amdgcn_wave_barrier();
+                        if (L < rest) qu[L] = keep;
+                        qn = rest;
+                        __builtin_amdgcn_wave_barrier();
+                    }
+                }
+            }
+            if (qn) quad_drain<W>(qu, qn, sS, ST, sCnt64);
+        }
+        __syncthreads();
+        for (int i = t; i < dd; i += BT) {
+            u64 c;
+            if constexpr (R == 2) c = sCnt2[i];
+            else if constexpr (R == 3) c = cnt[i] / 2;
+            else c = sCnt64[i] / 3;
+            if (c) ctx.add(sC[i], c);
+            if constexpr (R >= 3) tot += c;
+        }
+        if constexpr (R == 2) tot = L == 0 ? 2 * hits : 0;
+        tot = wave_sum(tot);
+        if (L == 0) sTot[wv] = tot;
+        __syncthreads();
+        if (t == 0) {
+            u64 s = 0;
+            for (int q = 0; q < NW; q++) s += sTot[q];
+            if (s) ctx.add_prefix(it, s / (u64)R);
+        }
         __syncthreads();
     }
 }

@@ -57,18 +57,30 @@ __device__ __forceinline__ u64 binom_sat_dev(u64 x, int r) {
     return (u64)acc;
 }
 
-constexpr int NCLASS = 6;
+// Roots are binned by out-degree.  The bins up to 768 (R = 2: 2,048), and up
+// to 1,088 for R = 3, hold what k_engine_rows keeps in LDS: 257-512 apart from
+// 513-768 so that three workgroups fit a CU, 1,088 because 17-word rows are the
+// longest that fit beside the table (148 KB).  Beyond, the bitmap lives in
+// global memory.  A launch class (what the tuning calls a class) is one bin
+// or two neighbouring ones.
+constexpr int NBIN = 8;
+// first bin of every launch class, and the end
+__host__ __device__ constexpr int class_bin(int R, int c) {
+    return R <= 2 ? c : c <= 2 ? c : c == 3 ? 4 : c == 4 ? 6 : 7;
+}
 
-// class of a root by its out-degree; -1 = no clique can be rooted here
-__device__ __forceinline__ int root_class(int d, int R) {
+// bin of a root by its out-degree; -1 = no clique can be rooted here
+__device__ __forceinline__ int root_bin(int d, int R) {
     if (d < R) return -1;
     if (d <= 64) return 0;
     if (R <= 2) return d <= 2048 ? 1 : 2;
     if (d <= 256) return 1;
-    if (d <= 768) return 2;
-    if (d <= 1280) return 3;
-    if (d <= 2048) return 4;
-    return 5;   // beyond the bitmap kernels
+    if (d <= 512) return 2;
+    if (d <= 768) return 3;
+    if (d <= 1088 && R == 3) return 4;
+    if (d <= 1280) return 5;
+    if (d <= 2048) return 6;
+    return 7;   // beyond the bitmap kernels
 }
 
 __device__ __forceinline__ u64 sat_add(u64 a, u64 b) { return (a + b < a) ? ~0ull : a + b; }
@@ -86,10 +98,10 @@ __global__ void k_classify(const int64_t *row_ptr, const int64_t *dag_off, const
         int c = -1, d = 0;
         if (r < n && (!mask || mask[r])) {
             d = (int)(row_ptr[r + 1] - dag_off[r]);
-            c = root_class(d, R);
+            c = root_bin(d, R);
         }
         if (pass == 0 && c >= 0) b = sat_add(b, binom_sat_dev((u64)d, R));
-        for (int k = 0; k < NCLASS; k++) {
+        for (int k = 0; k < NBIN; k++) {
             u64 m = __ballot(c == k);
             if (!m) continue;
             int leader = __builtin_ctzll(m);
@@ -278,48 +290,75 @@ static int class_cap(int R, int c) {
     return it == t.cap.end() ? default_cap(R, c) : it->second;
 }
 
-// one class's launch; cap: its grid cap (gs_blocks bounds the global-bitmap classes)
+// one bin's launch; cap: its grid cap (gs_blocks bounds the global-bitmap bins)
 template <int R>
-static void launch_class(int c, int cap, const DevGraph &g, const EnumCtx &base, const int32_t *lists,
-                         const int32_t *off, const int32_t *cnt, hipStream_t s, Scratch &sc, int gs_blocks) {
+static void launch_bin(int c, int cap, const DevGraph &g, const EnumCtx &base, const int32_t *lists,
+                       const int32_t *off, const int32_t *cnt, hipStream_t s, Scratch &sc, int gs_blocks) {
+    if (!cnt[c]) return;
     EnumCtx ctx = base;
     ctx.roots = lists + off[c];
+    const int blocks = grid_for(cnt[c], 1, cap);
     if (c == 0) {
-        const int blocks = grid_for(cnt[0], WAVES_PER_BLOCK, cap);
-        k_engine_wave<R, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off, cnt[0], nullptr);
+        k_engine_wave<R, EnumCtx><<<grid_for(cnt[0], WAVES_PER_BLOCK, cap), BLOCK, 0, s>>>(ctx, g.row_ptr, g.col,
+                                                                                         g.dag_off, cnt[0], nullptr);
         return;
     }
     if constexpr (R <= 2) {
-        if (c == 1) {
-            const int blocks = grid_for(cnt[1], 1, cap);
-            k_engine_block<R, 2048, 12, 1, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
-                                                                                     cnt[1], nullptr, nullptr);
-        } else if (c == 2) {
-            const int blocks = grid_for(cnt[2], 1, cap);
+        if (c == 1)
+            k_engine_rows<R, 2048, 12, 1, 256, EnumCtx><<<blocks, 256, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off, cnt[1]);
+        else
             k_engine_huge_r2<EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off, cnt[2], nullptr);
-        }
     } else {
+        const int gblocks = std::min(blocks, gs_blocks);
         if (c == 1) {
-            const int blocks = grid_for(cnt[1], 1, cap);
-            k_engine_block<R, 256, 9, 4, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
-                                                                                   cnt[1], nullptr, nullptr);
+            if constexpr (R <= 4)
+                k_engine_rows<R, 256, 10, 4, 256, EnumCtx><<<blocks, 256, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off, cnt[1]);
+            else
+                k_engine_block<R, 256, 9, 4, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                       cnt[1], nullptr, nullptr);
         } else if (c == 2) {
-            const int blocks = grid_for(cnt[2], 1, cap);
-            k_engine_block<R, 768, 11, 12, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col,
-                                                                                     g.dag_off, cnt[2], nullptr, nullptr);
+            if constexpr (R <= 4)
+                k_engine_rows<R, 512, 11, 8, 256, EnumCtx><<<blocks, 256, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off, cnt[2]);
+            else
+                k_engine_block<R, 512, 11, 8, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                        cnt[2], nullptr, nullptr);
         } else if (c == 3) {
-            const int blocks = grid_for(cnt[3], 1, std::min(cap, gs_blocks));
-            u64 *gS = sc.get_n<u64>((int64_t)blocks * 1280 * 20);
-            k_engine_block<R, 1280, 12, 20, true, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
-                                                                                    cnt[3], nullptr, gS);
+            if constexpr (R <= 4)
+                k_engine_rows<R, 768, 12, 12, 512, EnumCtx><<<blocks, 512, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                    cnt[3]);
+            else
+                k_engine_block<R, 768, 11, 12, false, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                         cnt[3], nullptr, nullptr);
         } else if (c == 4) {
+            if constexpr (R == 3)
+                k_engine_rows<R, 1088, 11, 17, 512, EnumCtx><<<blocks, 512, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                     cnt[4]);
+        } else if (c == 5) {
+            u64 *gS = sc.get_n<u64>((int64_t)gblocks * 1280 * 20);
+            k_engine_block<R, 1280, 12, 20, true, EnumCtx><<<gblocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                      cnt[5], nullptr, gS);
+        } else if (c == 6) {
             // hubs of out-degree 1281..2048: 32-word bitmap rows in global memory
-            const int blocks = grid_for(cnt[4], 1, std::min(cap, gs_blocks));
-            u64 *gS = sc.get_n<u64>((int64_t)blocks * 2048 * 32);
-            k_engine_block<R, 2048, 12, 32, true, EnumCtx><<<blocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
-                                                                                    cnt[4], nullptr, gS);
+            u64 *gS = sc.get_n<u64>((int64_t)gblocks * 2048 * 32);
+            k_engine_block<R, 2048, 12, 32, true, EnumCtx><<<gblocks, BLOCK, 0, s>>>(ctx, g.row_ptr, g.col, g.dag_off,
+                                                                                      cnt[6], nullptr, gS);
         }
     }
+}
+
+// one class's launches
+template <int R>
+static void launch_class(int c, int cap, const DevGraph &g, const EnumCtx &base, const int32_t *lists,
+                         const int32_t *off, const int32_t *cnt, hipStream_t s, Scratch &sc, int gs_blocks) {
+    for (int k = class_bin(R, c); k < class_bin(R, c + 1); k++)
+        launch_bin<R>(k, cap, g, base, lists, off, cnt, s, sc, gs_blocks);
+}
+
+// roots of launch class c
+static int32_t class_roots(int R, int c, const int32_t *cnt) {
+    int32_t n = 0;
+    for (int k = class_bin(R, c); k < class_bin(R, c + 1); k++) n += cnt[k];
+    return n;
 }
 
 static int nclass_of(int R) { return R <= 2 ? 3 : 5; }
@@ -328,7 +367,7 @@ template <int R>
 static void launch_engine(const DevGraph &g, const EnumCtx &base, const int32_t *lists, const int32_t *off,
                           const int32_t *cnt, hipStream_t s, Scratch &sc, int gs_blocks) {
     for (int c = 0; c < nclass_of(R); c++)
-        if (cnt[c]) launch_class<R>(c, class_cap(R, c), g, base, lists, off, cnt, s, sc, gs_blocks);
+        if (class_roots(R, c, cnt)) launch_class<R>(c, class_cap(R, c), g, base, lists, off, cnt, s, sc, gs_blocks);
 }
 
 static void launch_one_class(int R, int c, int cap, const DevGraph &g, const EnumCtx &ctx, const int32_t *lists,
@@ -346,16 +385,16 @@ static void launch_one_class(int R, int c, int cap, const DevGraph &g, const Enu
 // counts could overflow 64 bits.  The host copy of off must outlive the
 // stream's use of d_off (the callers synchronise before returning).
 struct RootClasses {
-    int32_t hc[NCLASS];
-    int32_t off[NCLASS + 1];
+    int32_t hc[NBIN];
+    int32_t off[NBIN + 1];
     int32_t *lists = nullptr;
 };
 static bool classify_roots(const DevGraph &g, int h, const uint8_t *mask, hipStream_t s, Scratch &sc, RootClasses &rc) {
     const int32_t n = g.n;
     const int R = h - 1;
-    int32_t *cursor = sc.get_n<int32_t>(NCLASS);
+    int32_t *cursor = sc.get_n<int32_t>(NBIN);
     u64 *bound = sc.get_n<u64>(1);
-    fill_i32(cursor, 0, NCLASS, s);
+    fill_i32(cursor, 0, NBIN, s);
     fill_u64(bound, 0, 1, s);
     int blocks = grid_for(n, BLOCK, 4096);
     k_classify<<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, 0, cursor, nullptr, nullptr, bound);
@@ -364,13 +403,13 @@ static bool classify_roots(const DevGraph &g, int h, const uint8_t *mask, hipStr
     DSD_HIP(hipMemcpyAsync(&hb, bound, sizeof(u64), hipMemcpyDeviceToHost, s));
     DSD_HIP(hipStreamSynchronize(s));
     if (hb == ~0ull || hb > ~0ull / (u64)h) return false;          // counts could overflow 64 bits
-    if (rc.hc[5]) throw Error(-5, "an out-neighbourhood exceeds 2048 vertices (limit of the bitmap kernels, h >= 4)");
+    if (rc.hc[7]) throw Error(-5, "an out-neighbourhood exceeds 2048 vertices (limit of the bitmap kernels, h >= 4)");
     rc.off[0] = 0;
-    for (int c = 0; c < NCLASS; c++) rc.off[c + 1] = rc.off[c] + rc.hc[c];
-    rc.lists = sc.get_n<int32_t>(rc.off[NCLASS]);
-    int32_t *d_off = sc.get_n<int32_t>(NCLASS + 1);
+    for (int c = 0; c < NBIN; c++) rc.off[c + 1] = rc.off[c] + rc.hc[c];
+    rc.lists = sc.get_n<int32_t>(rc.off[NBIN]);
+    int32_t *d_off = sc.get_n<int32_t>(NBIN + 1);
     DSD_HIP(hipMemcpyAsync(d_off, rc.off, sizeof(rc.off), hipMemcpyHostToDevice, s));
-    fill_i32(cursor, 0, NCLASS, s);
+    fill_i32(cursor, 0, NBIN, s);
     k_classify<<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, 1, cursor, rc.lists, d_off, bound);
     return true;
 }
@@ -408,7 +447,7 @@ bool clique_degrees(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hip
         float ms = 0;
         DSD_HIP(hipEventElapsedTime(&ms, e0, e1));
         kt->k3_ms += ms;
-        for (int c = 0; c < NCLASS; c++) kt->k3_launches += rc.hc[c] ? 1 : 0;
+        for (int c = 0; c < nclass_of(R); c++) kt->k3_launches += class_roots(R, c, rc.hc) ? 1 : 0;
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
     }
@@ -434,16 +473,17 @@ std::vector<TuneResult> autotune(const DevGraph &g, int h, hipStream_t s, Scratc
     DSD_HIP(hipEventCreate(&e1));
     const std::string arch = arch_name();
     for (int c = 0; c < nclass_of(R); c++) {
-        if (!rc.hc[c]) continue;
+        const int32_t roots = class_roots(R, c, rc.hc);
+        if (!roots) continue;
         // caps in workgroups; the wave class counts four roots a workgroup
         const int per = c == 0 ? WAVES_PER_BLOCK : 1;
-        const int need = (int)std::min<int64_t>(((int64_t)rc.hc[c] + per - 1) / per, 1 << 20);
+        const int need = (int)std::min<int64_t>(((int64_t)roots + per - 1) / per, 1 << 20);
         const bool global = R >= 3 && c >= 3;
         std::vector<int> cands = global ? std::vector<int>{64, 128, 256, 512, 1024}
                                         : std::vector<int>{256, 512, 1024, 2048, 4096, 8192};
         const int def = default_cap(R, c);
         if (std::find(cands.begin(), cands.end(), def) == cands.end()) cands.push_back(def);
-        TuneResult tr{c, rc.hc[c], def, def, 0.0, 0.0};
+        TuneResult tr{c, roots, def, def, 0.0, 0.0};
         std::map<int, double> seen;   // by effective grid
         double best = 1e300;
         for (int cap : cands) {
