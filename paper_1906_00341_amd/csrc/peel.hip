@@ -2340,8 +2340,9 @@ __global__ void k_start_graphs(PeelBufs b) {
 
 // ---------------------------------------------------------------- tail engine (h = 3 with triangle lists, h = 2)
 //
-// Once at most TE_MAX vertices are alive, the rest of a single graph's peel
-// runs in one launch of one workgroup.  First every CU helps to rewrite the
+// Once at most TE_MAX vertices of a graph are alive, the rest of its peel
+// runs in one launch of one workgroup (a batch: one workgroup per graph, and
+// no graph waits for another).  First every CU helps to rewrite the
 // tail vertices' rows (h = 3: triangle rows; h = 2: adjacency rows): only
 // pairs whose two vertices are still in the tail stay, renumbered to local
 // ids that follow the rank order (so the owner rule compares local ids),
@@ -2352,15 +2353,18 @@ __global__ void k_start_graphs(PeelBufs b) {
 // level at the smallest alive degree), the frontier, and the frontier's rows
 // streamed from HBM.  Each lane takes TE_PL consecutive pairs of a row with
 // vector loads, looks up all of their states before it waits, and applies
-// each run of one first vertex with a single LDS atomic.
+// each run of one first vertex with a single LDS atomic.  In min-degree mode
+// every round opens a level.
 
 constexpr int TE_MAX = (int)TAIL_ENGINE_VERTICES;   // tail vertices: local ids fit 16 bits
-constexpr int TE_BLOCK = 1024;
-constexpr int TE_WAVES = TE_BLOCK / WAVE;
-constexpr int TE_PER = TE_MAX / TE_BLOCK;     // local ids per thread in the frontier scans
+// A workgroup of BT threads holds PER BT vertices: 1,024 threads and 16 a thread
+// above 4,096, 4 a thread up to there, 512 threads up to 2,048 (29 KB of LDS, so
+// the waves a CU holds bound the graphs of a batch on it).
+constexpr int TE_PER = 16, TE_FEW = 4;
 constexpr int TE_PL = 8;                      // consecutive pairs per lane
 constexpr int TE_ITEM = WAVE * TE_PL;         // pairs per work item of a round
-constexpr int TE_FB = 2048;                   // frontier vertices per batch of items
+constexpr uint32_t TE_SHORT = 8 * TE_PL;      // a row of at most so many pairs is taken by eight lanes
+constexpr int TE_FB = 2048;                   // listed vertices of a frontier (larger ones: in chunks of ids)
 constexpr int TE_CH = 4096;                   // pairs per item of the row rewrite
 constexpr uint32_t TE_NONE = 0xffffffffu;     // padding (local ids are below 2^14)
 constexpr uint8_t TE_DEAD = 0, TE_CUR = 1, TE_ALIVE = 2;
@@ -2381,7 +2385,7 @@ struct TeState {
     uint32_t *ipre;       // [nF + 1] each frontier vertex's first item; ipre[nF] = items
     uint32_t *imap;       // [items] item -> frontier position
     int32_t heavy;        // set when the engine stopped for a grid round
-    int32_t r, nlevels, open;
+    int32_t r, nlevels;
     uint32_t nF, items;
     u64 k, mu_alive;
     int64_t n_alive;
@@ -2390,11 +2394,17 @@ struct TeState {
     u64 rounds;           // grid rounds
 };
 
-// tail membership: alive, or in the pending frontier of the next round
-__global__ void k_te_flags(const int32_t *stamp, int32_t n, const PeelCtl *c, uint32_t *flag) {
-    const int32_t r = c->round;
-    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-        flag[v] = stamp[v] >= r ? 1u : 0u;
+// one graph of the tail: its index in the peel, its first local vertex, its vertices
+struct TeGraph {
+    int32_t g, base, A;
+};
+
+// tail membership: alive, or in the pending frontier of the next round (of a
+// graph that takes part: gbase[g] >= 0; nullptr: a single graph)
+__global__ void k_te_flags(PeelBufs b, const int32_t *gbase, uint32_t *flag) {
+    const int32_t r = b.ctl->round;
+    for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < b.n; v += (int64_t)gridDim.x * blockDim.x)
+        flag[v] = b.stamp[v] >= r && (!gbase || gbase[b.gid[v]] >= 0) ? 1u : 0u;
 }
 
 // local id -> vertex, and each tail vertex's rewrite items (roff: the
@@ -2419,7 +2429,8 @@ __global__ void k_te_glob(const uint32_t *flag, const uint32_t *loc, int32_t n, 
 template <bool FILL, int H>
 __global__ __launch_bounds__(BLOCK) void k_te_pairs(const int64_t *tvoff, const int32_t *tpairs, const uint32_t *flag,
                                                      const uint32_t *loc, const int32_t *glob, const int64_t *ib,
-                                                     int32_t A, int64_t NI, int64_t *kc, uint32_t *lp) {
+                                                     int32_t A, int64_t NI, int64_t *kc, uint32_t *lp,
+                                                     const int32_t *gid, const int32_t *gbase) {
     const int wv = threadIdx.x / WAVE;
     for (int64_t it = (int64_t)blockIdx.x * WAVES_PER_BLOCK + wv; it < NI; it += (int64_t)gridDim.x * WAVES_PER_BLOCK) {
         int32_t lo = 0, hi = A - 1;   // the item's vertex: the largest l with ib[l] <= it
@@ -2429,6 +2440,7 @@ __global__ __launch_bounds__(BLOCK) void k_te_pairs(const int64_t *tvoff, const 
             else hi = mid - 1;
         }
         const int32_t v = glob[lo];
+        const uint32_t gb = gbase ? (uint32_t)gbase[gid[v]] : 0u;   // local ids count from the graph's first vertex
         const int64_t e0 = tvoff[v] + (it - ib[lo]) * TE_CH, e1 = min(tvoff[v + 1], e0 + TE_CH);
         int64_t pos = FILL ? kc[it] : 0;
         for (int64_t base = e0; base < e1; base += WAVE) {
@@ -2439,11 +2451,11 @@ __global__ __launch_bounds__(BLOCK) void k_te_pairs(const int64_t *tvoff, const 
                 if (H == 3) {
                     const int32_t a = tpairs[2 * e], x = tpairs[2 * e + 1];
                     keep = flag[a] && flag[x];
-                    if (FILL && keep) val = (loc[a] << 16) | loc[x];
+                    if (FILL && keep) val = ((loc[a] - gb) << 16) | (loc[x] - gb);
                 } else {
                     const int32_t x = tpairs[e];
                     keep = flag[x] != 0;
-                    if (FILL && keep) val = (loc[x] << 16) | loc[x];
+                    if (FILL && keep) val = ((loc[x] - gb) << 16) | (loc[x] - gb);
                 }
             }
             const u64 m = __ballot(keep);
@@ -2531,15 +2543,17 @@ __device__ __forceinline__ uint32_t te_wave_prefix(uint32_t v, uint32_t *total) 
 // Workgroup reductions, double-buffered so that one barrier suffices: a
 // call writes one half and reads it after the barrier; the next call uses
 // the other half, and the call after that is behind the next call's barrier.
+template <int NW>
 struct TeRed {
-    uint32_t cnt[2][TE_WAVES];
-    uint32_t mn[2][TE_WAVES];
-    uint32_t sum[2][TE_WAVES];
+    uint32_t cnt[2][NW];
+    uint32_t mn[2][NW];
+    uint32_t sum[2][NW];
 };
 
 // exclusive prefix (return) and total (*ctot) of c, minimum of m (*mall) and
 // sum of s (*sall) over the workgroup; every thread calls it with the same par
-__device__ __forceinline__ uint32_t te_reduce(TeRed &R, int &par, uint32_t c, uint32_t m, uint32_t s, uint32_t *ctot,
+template <int NW>
+__device__ __forceinline__ uint32_t te_reduce(TeRed<NW> &R, int &par, uint32_t c, uint32_t m, uint32_t s, uint32_t *ctot,
                                               uint32_t *mall, uint32_t *sall) {
     const int wv = threadIdx.x / WAVE, L = lane();
     uint32_t wtot = 0;
@@ -2551,9 +2565,9 @@ __device__ __forceinline__ uint32_t te_reduce(TeRed &R, int &par, uint32_t c, ui
         R.sum[par][wv] = wsum;
     }
     te_sync();
-    const uint32_t ci = L < TE_WAVES ? R.cnt[par][L] : 0u;
-    const uint32_t mi = L < TE_WAVES ? R.mn[par][L] : 0xffffffffu;
-    const uint32_t si = L < TE_WAVES ? R.sum[par][L] : 0u;
+    const uint32_t ci = L < NW ? R.cnt[par][L] : 0u;
+    const uint32_t mi = L < NW ? R.mn[par][L] : 0xffffffffu;
+    const uint32_t si = L < NW ? R.sum[par][L] : 0u;
     const uint32_t before = te_wave_reduce<false>(L < wv ? ci : 0u);
     *ctot = te_wave_reduce<false>(ci);
     *mall = te_wave_reduce<true>(mi);
@@ -2562,120 +2576,29 @@ __device__ __forceinline__ uint32_t te_reduce(TeRed &R, int &par, uint32_t c, ui
     return before + pre;
 }
 
-// this thread's TE_PER local ids: their degrees and states
-__device__ __forceinline__ void te_load(const uint32_t *sDeg, const uint8_t *sSt, int l0, uint32_t *d,
-                                        uint32_t *st) {
-    const uint4 s4 = *(const uint4 *)(sSt + l0);
-    const uint32_t sw[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-        const uint4 d4 = *(const uint4 *)(sDeg + l0 + 4 * q);
-        d[4 * q] = d4.x;
-        d[4 * q + 1] = d4.y;
-        d[4 * q + 2] = d4.z;
-        d[4 * q + 3] = d4.w;
-#pragma unroll
-        for (int j = 0; j < 4; j++) st[4 * q + j] = (sw[q] >> (8 * j)) & 0xffu;
-    }
-}
+// A vertex's word in LDS: its degree in the low bits (below C(TE_MAX, 2) < 2^27),
+// its state above.  The states are those of round r with q = r mod 3: TQ_IN(q) is
+// the round's frontier, TQ_IN(q + 1) the next round's (still alive), TQ_IN(q - 1)
+// the last round's (dead: the round r marks them TQ_DEAD, so the code is free
+// again for round r + 2).  So a vertex joins the next frontier in the middle of a
+// round, and a round needs no pass that marks its frontier.
+constexpr uint32_t TQ_SHIFT = 29, TQ_DEG = (1u << TQ_SHIFT) - 1, TQ_DEAD = 4u << TQ_SHIFT;
+__device__ __forceinline__ constexpr uint32_t TQ_IN(int q) { return (uint32_t)(1 + q) << TQ_SHIFT; }
+// the frontier's count: pairs of its rows | rows of at most TE_SHORT pairs << 32 | longer rows << 48
+__device__ __forceinline__ uint32_t tq_short(u64 c) { return (uint32_t)(c >> 32) & 0xffffu; }
+__device__ __forceinline__ uint32_t tq_long(u64 c) { return (uint32_t)(c >> 48); }
 
-// the frontier flags of this thread's ids at level k
-__device__ __forceinline__ uint32_t te_mask(const uint32_t *d, const uint32_t *st, u64 k) {
-    uint32_t mask = 0;
-#pragma unroll
-    for (int j = 0; j < TE_PER; j++) mask |= (st[j] == TE_ALIVE && d[j] <= k) ? 1u << j : 0u;
-    return mask;
-}
-
-// pairs and items (TE_ITEM pairs each) in the rows of this thread's ids in mask
-__device__ __forceinline__ void te_front_work(uint32_t mask, int l0, const uint32_t *sRs, uint32_t *pairs,
-                                              uint32_t *items) {
-    uint32_t p = 0, it = 0;
-    for (uint32_t mm = mask; mm; mm &= mm - 1) {
-        const int l = l0 + __builtin_ctz(mm);
-        const uint32_t len = sRs[l + 1] - sRs[l];
-        p += len;
-        it += (len + TE_ITEM - 1) / TE_ITEM;
-    }
-    *pairs = p;
-    *items = it;
-}
-
-// A round's frontier from one exchange between the waves.  Each wave offers
-// two candidates: its alive ids of degree <= k, and its alive ids at the
-// wave's smallest degree; with their counts, item counts and pairs, and the
-// previous round's destroyed cliques.  Once the exchange is read, either some
-// ids are at degree <= k (the level goes on with them) or none is, and the
-// new level opens at the smallest alive degree with the ids of the waves
-// whose own minimum it is.  The frontier position (at) and first item (iat)
-// of this thread's ids are exclusive prefixes in id order.
-struct TeSel {
-    uint32_t v[2][8][TE_WAVES];   // [parity][field][wave]
-};
-constexpr int TS_CK = 0, TS_CM = 1, TS_MIN = 2, TS_DEST = 3, TS_PK = 4, TS_PM = 5, TS_IK = 6, TS_IM = 7;
-struct TeRound {
-    uint32_t mask, nF, at, iat, items, fpairs, gone, gmin;
-    bool fresh;   // a new level at gmin
-};
-__device__ __forceinline__ TeRound te_select(TeSel &S, int &par, const uint32_t *d, const uint32_t *st, u64 k, int l0,
-                                             const uint32_t *sRs, uint32_t destroyed) {
-    const int wv = threadIdx.x / WAVE, L = lane();
-    const uint32_t mk = te_mask(d, st, k);
-    uint32_t mn = 0xffffffffu;
-#pragma unroll
-    for (int j = 0; j < TE_PER; j++)
-        if (st[j] == TE_ALIVE && d[j] < mn) mn = d[j];
-    const uint32_t wmin = te_wave_reduce<true>(mn);
-    uint32_t mm = 0;
-#pragma unroll
-    for (int j = 0; j < TE_PER; j++) mm |= (st[j] == TE_ALIVE && d[j] == wmin) ? 1u << j : 0u;
-    uint32_t pk, ik, pm, im;
-    te_front_work(mk, l0, sRs, &pk, &ik);
-    te_front_work(mm, l0, sRs, &pm, &im);
-    uint32_t ckw, cmw, ikw, imw;
-    const uint32_t prek = te_wave_prefix(__popc(mk), &ckw), prem = te_wave_prefix(__popc(mm), &cmw);
-    const uint32_t preik = te_wave_prefix(ik, &ikw), preim = te_wave_prefix(im, &imw);
-    const uint32_t dw = te_wave_reduce<false>(destroyed), pkw = te_wave_reduce<false>(pk),
-                   pmw = te_wave_reduce<false>(pm);
-    if (L == 0) {
-        S.v[par][TS_CK][wv] = ckw;
-        S.v[par][TS_CM][wv] = cmw;
-        S.v[par][TS_MIN][wv] = wmin;
-        S.v[par][TS_DEST][wv] = dw;
-        S.v[par][TS_PK][wv] = pkw;
-        S.v[par][TS_PM][wv] = pmw;
-        S.v[par][TS_IK][wv] = ikw;
-        S.v[par][TS_IM][wv] = imw;
-    }
-    te_sync();
-    const bool in = L < TE_WAVES;
-    const uint32_t ck = in ? S.v[par][TS_CK][L] : 0u, wm = in ? S.v[par][TS_MIN][L] : 0xffffffffu;
-    TeRound o;
-    o.gone = te_wave_reduce<false>(in ? S.v[par][TS_DEST][L] : 0u);
-    o.gmin = te_wave_reduce<true>(wm);
-    const uint32_t nfk = te_wave_reduce<false>(ck);
-    if (nfk > 0) {
-        const uint32_t ic = in ? S.v[par][TS_IK][L] : 0u;
-        o.fresh = false;
-        o.mask = mk;
-        o.nF = nfk;
-        o.at = prek + te_wave_reduce<false>(L < wv ? ck : 0u);
-        o.iat = preik + te_wave_reduce<false>(L < wv ? ic : 0u);
-        o.items = te_wave_reduce<false>(ic);
-        o.fpairs = te_wave_reduce<false>(in ? S.v[par][TS_PK][L] : 0u);
-    } else {
-        const bool eq = in && wm == o.gmin;
-        const uint32_t cm = eq ? S.v[par][TS_CM][L] : 0u, ic = eq ? S.v[par][TS_IM][L] : 0u;
-        o.fresh = true;
-        o.mask = wmin == o.gmin ? mm : 0u;
-        o.nF = te_wave_reduce<false>(cm);
-        o.at = prem + te_wave_reduce<false>(L < wv ? cm : 0u);
-        o.iat = preim + te_wave_reduce<false>(L < wv ? ic : 0u);
-        o.items = te_wave_reduce<false>(ic);
-        o.fpairs = te_wave_reduce<false>(eq ? S.v[par][TS_PM][L] : 0u);
-    }
-    par ^= 1;
-    return o;
+// exclusive prefix over the wave's lanes in DPP steps; *total: the sum
+__device__ __forceinline__ uint32_t te_wave_scan(uint32_t v, uint32_t *total) {
+    uint32_t s = v;
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x111, 0xf, 0xf, false);   // row shift 1, 2, 4, 8
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x112, 0xf, 0xf, false);
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x114, 0xf, 0xf, false);
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x118, 0xf, 0xf, false);
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x142, 0xa, 0xf, false);   // row 15 -> rows 1, 3
+    s += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)s, 0x143, 0xc, 0xf, false);   // lane 31 -> rows 2, 3
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)s, 63);
+    return s - v;
 }
 
 // lrow (A + 1 entries) below 2^32: the row starts live in LDS.  H = 2: a
@@ -2683,123 +2606,166 @@ __device__ __forceinline__ TeRound te_select(TeSel &S, int &par, const uint32_t 
 // resume: the state comes from ts, where the engine left it for a grid
 // round, and that round ends first.  A round whose frontier rows hold more
 // than heavy pairs is left to the grid.
-template <int H>
-__global__ __launch_bounds__(TE_BLOCK) void k_tail_engine(PeelBufs b, const int32_t *glob, const int64_t *lrow,
-                                                          const uint32_t *lp, int32_t A, int32_t *err, TeState *ts,
-                                                          int resume, uint32_t heavy) {
-    __shared__ __align__(16) uint32_t sDeg[TE_MAX];
-    __shared__ __align__(16) uint8_t sSt[TE_MAX];
-    __shared__ uint32_t sRs[TE_MAX + 1];
-    __shared__ uint16_t sF[TE_FB];
-    __shared__ uint32_t sIpre[TE_FB];
-    __shared__ TeRed R;
-    __shared__ TeSel S;
+// A workgroup takes the graph tg[blockIdx.x] (nullptr: the single graph, of A1
+// vertices); heavy is only below 2^32 - 1 for a single graph.  core_l: scratch,
+// the tail vertices' core numbers (min-degree mode: rounds) by local id.
+//
+// Small graphs and sparse tails are bound by the chain of dependent steps of a
+// round, so there is one barrier a round inside a level.  The thread whose subtraction takes a degree to k or below
+// puts the vertex on the next frontier's list, so only a new level looks all the
+// vertices over.  Rows of at most TE_SHORT pairs are taken by eight lanes each;
+// longer ones in items of TE_ITEM pairs by whole waves, every wave finding its
+// items in a scan of the listed rows' lengths that it makes for itself.  (With the
+// frontier selected anew each round, by eight reductions over the workgroup and a
+// binary search per item: 375 us for a G(n, p) of 2,000 vertices, h = 2, now 110;
+// 8.3 ms for a power-law graph of 30,011 vertices, h = 3, now 4.5.)  Dense tails
+// are bound by what one CU reads, about 8 B a cycle.
+template <int H, int BT, int PER>
+__global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *tg, int32_t A1, const int32_t *glob_all,
+                                                    const int64_t *lrow_all, const uint32_t *lp_all,
+                                                    uint32_t *core_all, int32_t *err, TeState *ts, int resume,
+                                                    uint32_t heavy, int32_t round0) {
+    constexpr int TEM = BT * PER, NW = BT / WAVE;
+    constexpr uint32_t FB = TEM < TE_FB ? TEM : TE_FB;
+    static_assert(FB >= BT, "a chunk of ids has to fit the list");
+    __shared__ __align__(16) uint32_t sDeg[TEM];
+    __shared__ uint32_t sRs[TEM + 1];
+    __shared__ uint16_t sF[3][FB];           // a frontier's short rows from the front, its long ones from the back
+    __shared__ u64 sCnt[3];
+    __shared__ uint32_t sOv;                 // a chunk's short rows | long ones << 16 (frontiers above FB)
+    __shared__ TeRed<NW> R;
     PeelCtl *c = b.ctl;
-    GraphState *gs = b.gs;
-    const int t = threadIdx.x, wv = t / WAVE, L = lane();
+    const TeGraph me = tg ? tg[blockIdx.x] : TeGraph{0, 0, A1};
+    const int32_t A = me.A;
+    GraphState *gs = b.gs + me.g;
+    const int32_t *glob = glob_all + me.base;
+    const int64_t *lrow = lrow_all + me.base;
+    const uint32_t *lp = lp_all + lrow[0];
+    uint32_t *core_l = core_all + me.base;
+    const bool minpeel = b.minpeel != 0;
+    const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t / WAVE), L = lane();
     int32_t r, nlevels;
     u64 k, mu_alive;
     int64_t n_alive;
     bool open;
-    uint32_t destroyed = 0;   // this thread's share of the current round (summed at the next round's start;
-                              // a round destroys at most mu_alive < 2^32 cliques)
+    uint32_t destroyed = 0;   // this thread's share since the last level opened (in all below mu_alive < 2^32)
     if (!resume) {
-        for (int l = t; l < TE_MAX; l += TE_BLOCK) {
-            sDeg[l] = l < A ? (uint32_t)b.deg[glob[l]] : 0u;
-            sSt[l] = l < A ? TE_ALIVE : TE_DEAD;
-        }
-        r = c->round;
+        for (int l = t; l < TEM; l += BT) sDeg[l] = l < A ? (uint32_t)b.deg[glob[l]] : TQ_DEAD;
+        r = tg ? round0 : c->round;   // (c->round moves while other graphs' workgroups finish)
         k = gs[0].k;
         mu_alive = gs[0].mu_alive;
         n_alive = gs[0].n_alive;
         nlevels = gs[0].nlevels;
         open = gs[0].sel != 0;
     } else {
-        for (int l = t; l < TE_MAX; l += TE_BLOCK) {
-            sDeg[l] = l < A ? ts->deg[l] : 0u;
-            sSt[l] = l < A ? ts->st[l] : TE_DEAD;
-        }
-        r = ts->r;
+        // the end of the round the grid processed
+        for (int l = t; l < TEM; l += BT) sDeg[l] = l < A && ts->st[l] == TE_ALIVE ? ts->deg[l] : TQ_DEAD;
+        r = ts->r + 1;
         k = ts->k;
         mu_alive = ts->mu_alive;
-        n_alive = ts->n_alive;
+        n_alive = ts->n_alive - ts->nF;
         nlevels = ts->nlevels;
-        open = ts->open != 0;
+        open = false;
         if (t == 0) destroyed = (uint32_t)ts->destroyed;
     }
-    for (int l = t; l <= A; l += TE_BLOCK) sRs[l] = (uint32_t)lrow[l];
+    for (int l = t; l <= A; l += BT) sRs[l] = (uint32_t)(lrow[l] - lrow[0]);
+    if (t < 3) sCnt[t] = 0;
     const int64_t lv_base = gs[0].lv_base;
-    int par = 0, spar = 0;
+    int par = 0;
     __syncthreads();
-    if (t == 0) ts->heavy = 0;
-    const int l0 = t * TE_PER;
-    if (resume) {
-        // the end of the round the grid processed
-        if (open) nlevels += 1;
-        n_alive -= ts->nF;
-        r += 1;
-        open = false;
-#pragma unroll
-        for (int j = 0; j < TE_PER; j++)
-            if (sSt[l0 + j] == TE_CUR) sSt[l0 + j] = TE_DEAD;
-    }
+    if (t == 0 && ts) ts->heavy = 0;
+    const int l0 = t * PER;
+    bool some = true;             // an id of this wave was alive when a level last opened
+    int q = 0;                    // the round mod 3
+    uint32_t pns = 0, pnF = 0;    // the last round's short rows and frontier
     int64_t guard = 0;
-    while (n_alive > 0) {
-        if (++guard > (int64_t)A + 1) {   // every round removes at least one vertex
-            if (t == 0) *err = 1;
+    for (;;) {
+        u64 cn = sCnt[q];
+        if (cn == 0) {
+            if (n_alive <= 0) break;
+            // no vertex was taken to k or below: a new level at the smallest
+            // alive degree (at the start: the vertices of degree <= k, if any)
+            uint32_t d[PER], mn = 0xffffffffu;
+            if (some) {
+#pragma unroll
+                for (int j = 0; j < PER / 4; j++) {
+                    const uint4 d4 = *(const uint4 *)(sDeg + l0 + 4 * j);
+                    d[4 * j] = d4.x;
+                    d[4 * j + 1] = d4.y;
+                    d[4 * j + 2] = d4.z;
+                    d[4 * j + 3] = d4.w;
+                }
+#pragma unroll
+                for (int j = 0; j < PER; j++) mn = min(mn, d[j] <= TQ_DEG ? d[j] : 0xffffffffu);
+                some = __ballot(mn != 0xffffffffu) != 0;
+            }
+            uint32_t u0, gmin, gone;
+            (void)te_reduce(R, par, 0u, mn, destroyed, &u0, &gmin, &gone);
+            destroyed = 0;
+            mu_alive -= gone;
+            if (minpeel || (u64)gmin > k) {
+                open = true;
+                k = gmin;
+            }
+            const uint32_t top = k < TQ_DEG ? (uint32_t)k : TQ_DEG;
+            if (mn <= top) {
+#pragma unroll
+                for (int j = 0; j < PER; j++) {
+                    if (d[j] > top) continue;
+                    const uint32_t len = sRs[l0 + j + 1] - sRs[l0 + j];
+                    const bool lg = len > TE_SHORT;
+                    const u64 o = atomicAdd((unsigned long long *)&sCnt[q], (1ull << (lg ? 48 : 32)) + len);
+                    const uint32_t ns = tq_short(o), nl = tq_long(o);
+                    if (ns + nl < FB) sF[q][lg ? FB - 1 - nl : ns] = (uint16_t)(l0 + j);
+                    sDeg[l0 + j] = d[j] | TQ_IN(q);
+                }
+            }
+            // the level table entry of a new level: the level, |R_k| and mu(R_k)
+            // as its first round begins
+            if (open) {
+                if (t == 0) {
+                    const int64_t at_l = lv_base + nlevels;
+                    b.lv_k[at_l] = k;
+                    b.lv_size[at_l] = (u64)n_alive;
+                    b.lv_mu[at_l] = mu_alive;
+                }
+                nlevels += 1;
+                open = false;
+            }
+            te_sync();
+            cn = sCnt[q];
+        }
+        const uint32_t ns = tq_short(cn), nl = tq_long(cn), nF = ns + nl, fpairs = (uint32_t)cn;
+        if (nF == 0 || ++guard > (int64_t)A + 1) {   // cannot happen: every round removes at least one vertex
+            if (t == 0) *err = nF == 0 ? 2 : 1;
             break;
         }
-        // the frontier: alive vertices of degree <= k; none left means a new
-        // level at the smallest alive degree.  The same reduction ends the
-        // previous round (its destroyed cliques).
-        TeRound rd;
-        {
-            uint32_t d[TE_PER], st[TE_PER];
-            te_load(sDeg, sSt, l0, d, st);
-            rd = te_select(S, spar, d, st, k, l0, sRs, destroyed);
-        }
-        destroyed = 0;
-        mu_alive -= rd.gone;
-        if (rd.fresh) {
-            open = true;
-            k = k > (u64)rd.gmin ? k : (u64)rd.gmin;
-        }
-        const uint32_t mask = rd.mask, nF = rd.nF, at = rd.at, fpairs = rd.fpairs;
-        if (nF == 0) {   // cannot happen while vertices are alive
-            if (t == 0) *err = 2;
-            break;
-        }
-        // the level table entry of a new level: the level, |R_k| and mu(R_k)
-        // as its first round begins
-        if (open && t == 0) {
-            const int64_t at_l = lv_base + nlevels;
-            b.lv_k[at_l] = k;
-            b.lv_size[at_l] = (u64)n_alive;
-            b.lv_mu[at_l] = mu_alive;
-        }
-        // frontier vertices leave: a removed vertex's degree slot keeps its
-        // core number (written out at the end)
-        for (uint32_t mm = mask; mm; mm &= mm - 1) {
-            const int l = l0 + __builtin_ctz(mm);
-            sSt[l] = TE_CUR;
-            sDeg[l] = (uint32_t)k;
-        }
+        const int qn = q == 2 ? 0 : q + 1, qp = q == 0 ? 2 : q - 1;
+        // a vertex's core number (min-degree mode: its round)
+        const uint32_t label = minpeel ? (uint32_t)r : (uint32_t)k;
         if (fpairs > heavy) {
             // a heavy round goes to the grid: the frontier with its items'
             // starts, and the whole state, to ts; then the engine stops
-            const uint32_t items = rd.items;
-            uint32_t run = rd.iat;
-            te_sync();   // orders the frontier marks before the state is copied
-            uint32_t q = at;
-            for (uint32_t mm = mask; mm; mm &= mm - 1, q++) {
+            uint32_t mask = 0, own = 0;
+            for (int j = 0; j < PER; j++) {
+                if ((sDeg[l0 + j] & ~TQ_DEG) != TQ_IN(q)) continue;
+                mask |= 1u << j;
+                own += (sRs[l0 + j + 1] - sRs[l0 + j] + TE_ITEM - 1) / TE_ITEM;
+            }
+            uint32_t cnt, items, gone, u0, u1;
+            uint32_t at = te_reduce(R, par, (uint32_t)__popc(mask), 0u, destroyed, &cnt, &u0, &gone);
+            uint32_t run = te_reduce(R, par, own, 0u, 0u, &items, &u0, &u1);
+            for (uint32_t mm = mask; mm; mm &= mm - 1, at++) {
                 const int l = l0 + __builtin_ctz(mm);
-                ts->F[q] = (uint32_t)l;
-                ts->ipre[q] = run;
+                ts->F[at] = (uint32_t)l;
+                ts->ipre[at] = run;
+                core_l[l] = label;
                 run += (sRs[l + 1] - sRs[l] + TE_ITEM - 1) / TE_ITEM;
             }
-            for (int l = t; l < A; l += TE_BLOCK) {
-                ts->deg[l] = sDeg[l];
-                ts->st[l] = sSt[l];
+            for (int l = t; l < A; l += BT) {
+                const uint32_t w = sDeg[l], st = w & ~TQ_DEG;
+                ts->deg[l] = w & TQ_DEG;
+                ts->st[l] = st == 0 ? TE_ALIVE : st == TQ_IN(q) ? TE_CUR : TE_DEAD;
             }
             if (t == 0) {
                 ts->ipre[nF] = items;
@@ -2807,10 +2773,9 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tail_engine(PeelBufs b, const int3
                 ts->items = items;
                 ts->r = r;
                 ts->k = k;
-                ts->mu_alive = mu_alive;
+                ts->mu_alive = mu_alive - gone;
                 ts->n_alive = n_alive;
                 ts->nlevels = nlevels;
-                ts->open = open ? 1 : 0;
                 ts->destroyed = 0;
                 ts->pairs += fpairs;
                 ts->rounds += 1;
@@ -2818,136 +2783,150 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tail_engine(PeelBufs b, const int3
             }
             return;
         }
-        // the frontier's rows: the nb vertices listed in sF, their items'
-        // starts in sIpre
-        auto run_items = [&](int nb, uint32_t items) {
-            // each wave takes items wv, wv + TE_WAVES, ...; the next one's
-            // pairs are loaded while the current one is processed
-            auto locate = [&](uint32_t it, uint32_t *v, uint32_t *p0, uint32_t *p1) {
-                int lo = 0, hi = nb - 1;   // the item's frontier vertex: the largest q with sIpre[q] <= it
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (sIpre[mid] <= it) lo = mid;
-                    else hi = mid - 1;
-                }
-                const uint32_t l = sF[lo], ofs = (it - sIpre[lo]) * TE_ITEM;
-                *v = l;
-                *p0 = sRs[l] + ofs;
-                *p1 = min(sRs[l + 1], *p0 + TE_ITEM);
-            };
-            auto fetch = [&](uint32_t p0, uint32_t p1, uint32_t *pv) {
-                const uint32_t q0 = p0 + (uint32_t)L * TE_PL;
-#pragma unroll
-                for (int cq = 0; cq < TE_PL / 4; cq++) {
-                    uint4 w = make_uint4(TE_NONE, TE_NONE, TE_NONE, TE_NONE);
-                    if (q0 + 4 * cq < p1) w = *(const uint4 *)(lp + q0 + 4 * cq);
-                    pv[4 * cq] = w.x;
-                    pv[4 * cq + 1] = w.y;
-                    pv[4 * cq + 2] = w.z;
-                    pv[4 * cq + 3] = w.w;
-                }
-            };
-            uint32_t v = 0, pv[TE_PL], p0 = 0, p1 = 0;
-            if ((uint32_t)wv < items) {
-                locate(wv, &v, &p0, &p1);
-                fetch(p0, p1, pv);
-            }
-            for (uint32_t it = wv; it < items; it += TE_WAVES) {
-                uint32_t vn = 0, pn[TE_PL];
-#pragma unroll
-                for (int j = 0; j < TE_PL; j++) pn[j] = TE_NONE;
-                if (it + TE_WAVES < items) {
-                    locate(it + TE_WAVES, &vn, &p0, &p1);
-                    fetch(p0, p1, pn);
-                }
-                uint32_t s2[TE_PL];   // states of a (low byte) and x (next byte)
-#pragma unroll
-                for (int j = 0; j < TE_PL; j++) {
-                    const uint32_t qv = pv[j] == TE_NONE ? 0u : pv[j];
-                    s2[j] = (uint32_t)sSt[qv >> 16] | ((uint32_t)sSt[qv & 0xffffu] << 8);
-                }
-                // triangle {v, a, x} costs a and x a clique each: x's loss goes
-                // at once (0 for a removed vertex; a padding word touches slot
-                // 0 with 0), a's are summed over the lane's run of equal a
-                uint32_t acc = 0;
-#pragma unroll
-                for (int j = 0; j < TE_PL; j++) {
-                    const uint32_t qv = pv[j] == TE_NONE ? 0u : pv[j];
-                    const uint32_t a = qv >> 16, x = qv & 0xffffu;
-                    const uint32_t sa = s2[j] & 0xffu, sx = s2[j] >> 8;
-                    const bool ok = pv[j] != TE_NONE && te_allowed(sa, a, v) && te_allowed(sx, x, v);
-                    destroyed += ok ? 1u : 0u;
-                    if (H == 3) atomicSub(&sDeg[x], (ok && sx == TE_ALIVE) ? 1u : 0u);
-                    acc += (ok && sa == TE_ALIVE) ? 1u : 0u;
-                    const bool last = j == TE_PL - 1 || (pv[j + (j < TE_PL - 1)] >> 16) != a;
-                    if (last && acc) {
-                        atomicSub(&sDeg[a], acc);
-                        acc = 0;
-                    }
-                }
-                v = vn;
-#pragma unroll
-                for (int j = 0; j < TE_PL; j++) pv[j] = pn[j];
-            }
-            te_sync();   // the next batch rewrites sF and sIpre; the next round reads the degrees
-        };
-        if (nF <= TE_FB) {
-            // one batch: the list and the item starts come from the selection
-            uint32_t q = at, ip = rd.iat;
-            for (uint32_t mm = mask; mm; mm &= mm - 1, q++) {
-                const int l = l0 + __builtin_ctz(mm);
-                sF[q] = (uint16_t)l;
-                sIpre[q] = ip;
-                ip += (sRs[l + 1] - sRs[l] + TE_ITEM - 1) / TE_ITEM;
-            }
-            te_sync();
-            run_items((int)nF, rd.items);
+        // the last frontier is dead for good, and its count is the next but one's
+        if (t == 0) sCnt[qp] = 0;
+        if (pnF <= FB) {
+            for (uint32_t i = t; i < pnF; i += BT) sDeg[sF[qp][i < pns ? i : FB - 1 - (i - pns)]] = TQ_DEAD;
         } else {
-            // TE_FB vertices at a time
-            for (uint32_t f0 = 0; f0 < nF; f0 += TE_FB) {
-                const int nb = (int)min((uint32_t)TE_FB, nF - f0);
-                uint32_t q = at;
-                for (uint32_t mm = mask; mm; mm &= mm - 1, q++)
-                    if (q >= f0 && q < f0 + TE_FB) sF[q - f0] = (uint16_t)(l0 + __builtin_ctz(mm));
-                te_sync();
-                constexpr int PT = TE_FB / TE_BLOCK;
-                uint32_t cnt[PT], own = 0;
+            for (int j = 0; j < PER; j++)
+                if ((sDeg[l0 + j] & ~TQ_DEG) == TQ_IN(qp)) sDeg[l0 + j] = TQ_DEAD;
+        }
+        // inside a level, the vertices that fall to k or below join the next frontier
+        const uint32_t kx = minpeel || k > TQ_DEG ? TQ_DEG : (uint32_t)k;
+        const uint32_t inn = TQ_IN(qn), cur = TQ_IN(q);
+        auto push = [&](uint32_t l) {
+            const uint32_t len = sRs[l + 1] - sRs[l];
+            const bool lg = len > TE_SHORT;
+            atomicAdd(&sDeg[l], inn);
+            const u64 o = atomicAdd((unsigned long long *)&sCnt[qn], (1ull << (lg ? 48 : 32)) + len);
+            const uint32_t ps = tq_short(o), pl = tq_long(o);
+            if (ps + pl < FB) sF[qn][lg ? FB - 1 - pl : ps] = (uint16_t)l;
+        };
+        auto fetch = [&](uint32_t q0, uint32_t p1, uint32_t *pv) {
 #pragma unroll
-                for (int j = 0; j < PT; j++) {
-                    const int qq = t * PT + j;
-                    cnt[j] = 0;
-                    if (qq < nb) {
-                        const uint32_t l = sF[qq];
-                        cnt[j] = (sRs[l + 1] - sRs[l] + TE_ITEM - 1) / TE_ITEM;
-                    }
-                    own += cnt[j];
-                }
-                uint32_t items = 0, u1, u2;
-                uint32_t run = te_reduce(R, par, own, 0xffffffffu, 0u, &items, &u1, &u2);
+            for (int cq = 0; cq < TE_PL / 4; cq++) {
+                uint4 w = make_uint4(TE_NONE, TE_NONE, TE_NONE, TE_NONE);
+                if (q0 + 4 * cq < p1) w = *(const uint4 *)(lp + q0 + 4 * cq);
+                pv[4 * cq] = w.x;
+                pv[4 * cq + 1] = w.y;
+                pv[4 * cq + 2] = w.z;
+                pv[4 * cq + 3] = w.w;
+            }
+        };
+        // a lane's TE_PL pairs of v's row
+        auto pairs = [&](uint32_t v, const uint32_t *pv) {
+            uint32_t da[TE_PL], dx[TE_PL];
 #pragma unroll
-                for (int j = 0; j < PT; j++) {
-                    const int qq = t * PT + j;
-                    if (qq < nb) sIpre[qq] = run;
-                    run += cnt[j];
+            for (int j = 0; j < TE_PL; j++) {
+                const uint32_t qv = pv[j] == TE_NONE ? 0u : pv[j];
+                da[j] = sDeg[qv >> 16] & ~TQ_DEG;
+                if (H == 3) dx[j] = sDeg[qv & 0xffffu] & ~TQ_DEG;
+            }
+            // triangle {v, a, x} costs a and x a clique each: x's loss goes
+            // at once, a's are summed over the lane's run of equal a
+            uint32_t acc = 0, ca[TE_PL], oa[TE_PL], ox[TE_PL];
+#pragma unroll
+            for (int j = 0; j < TE_PL; j++) {
+                const uint32_t a = pv[j] >> 16, x = pv[j] & 0xffffu;
+                const bool la = da[j] == 0 || da[j] == inn, lx = H == 2 || dx[j] == 0 || dx[j] == inn;
+                const bool ok = pv[j] != TE_NONE && (la || (da[j] == cur && a > v)) &&
+                                (H == 2 || lx || (dx[j] == cur && x > v));
+                destroyed += ok ? 1u : 0u;
+                ox[j] = 0;
+                if (H == 3 && ok && lx) ox[j] = atomicSub(&sDeg[x], 1u);
+                acc += (ok && la) ? 1u : 0u;
+                const bool last = H == 2 || j == TE_PL - 1 || (pv[j + (j < TE_PL - 1)] >> 16) != a;
+                ca[j] = last ? acc : 0u;
+                oa[j] = 0;
+                if (ca[j]) oa[j] = atomicSub(&sDeg[a], ca[j]);
+                acc = last ? 0u : acc;
+            }
+#pragma unroll
+            for (int j = 0; j < TE_PL; j++) {
+                const uint32_t a = pv[j] >> 16, x = pv[j] & 0xffffu;
+                const uint32_t pa = oa[j] & TQ_DEG;
+                if (H == 3 && (ox[j] & TQ_DEG) == kx + 1) push(x);
+                if (pa > kx && pa - ca[j] <= kx) push(a);
+            }
+        };
+        auto run_rows = [&](uint32_t nshort, uint32_t nlong) {
+            // short rows: eight lanes each
+            for (uint32_t e = t / (TE_SHORT / TE_PL); e < nshort; e += BT / (TE_SHORT / TE_PL)) {
+                const uint32_t v = sF[q][e], p1 = sRs[v + 1];
+                uint32_t pv[TE_PL];
+                fetch(sRs[v] + (uint32_t)(t % (TE_SHORT / TE_PL)) * TE_PL, p1, pv);
+                pairs(v, pv);
+            }
+            // long rows, 64 at a time: a wave takes items wv, wv + NW, ...; the
+            // next one's pairs are loaded while the current one is processed
+            uint32_t first = wv;
+            for (uint32_t e0 = 0; e0 < nlong; e0 += WAVE) {
+                const uint32_t e = e0 + L;
+                const uint32_t v = e < nlong ? sF[q][FB - 1 - e] : 0u;
+                const uint32_t p0 = e < nlong ? sRs[v] : 0u, p1 = e < nlong ? sRs[v + 1] : 0u;
+                uint32_t items;
+                const uint32_t pre = te_wave_scan((p1 - p0 + TE_ITEM - 1) / TE_ITEM, &items);
+                auto get = [&](uint32_t it, uint32_t *vi, uint32_t *pv) {
+                    const int at = __popcll(__ballot(pre <= it)) - 1;   // the item's row: the last that starts at or before it
+                    *vi = (uint32_t)__builtin_amdgcn_readlane((int)v, at);
+                    const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)p0, at) +
+                                        (it - (uint32_t)__builtin_amdgcn_readlane((int)pre, at)) * TE_ITEM;
+                    fetch(b0 + (uint32_t)L * TE_PL, (uint32_t)__builtin_amdgcn_readlane((int)p1, at), pv);
+                };
+                uint32_t vi = 0, pv[TE_PL];
+                uint32_t it = first;
+                if (it < items) get(it, &vi, pv);
+                for (; it < items; it += NW) {
+                    uint32_t vn = 0, pn[TE_PL];
+#pragma unroll
+                    for (int j = 0; j < TE_PL; j++) pn[j] = TE_NONE;
+                    if (it + NW < items) get(it + NW, &vn, pn);
+                    pairs(vi, pv);
+                    vi = vn;
+#pragma unroll
+                    for (int j = 0; j < TE_PL; j++) pv[j] = pn[j];
+                }
+                first = it - items;   // the next rows go on with the next wave
+            }
+        };
+        if (nF <= FB) {
+            for (uint32_t i = t; i < nF; i += BT) core_l[sF[q][i < ns ? i : FB - 1 - (i - ns)]] = label;
+            run_rows(ns, nl);
+        } else {
+            // a frontier that the list does not hold, BT ids at a time
+            for (int j = 0; j < PER; j++) {
+                if (t == 0) sOv = 0;
+                te_sync();
+                const uint32_t l = (uint32_t)(j * BT + t);
+                if ((sDeg[l] & ~TQ_DEG) == cur) {
+                    const bool lg = sRs[l + 1] - sRs[l] > TE_SHORT;
+                    const uint32_t o = atomicAdd(&sOv, lg ? 0x10000u : 1u);
+                    sF[q][lg ? FB - 1 - (o >> 16) : (o & 0xffffu)] = (uint16_t)l;
+                    core_l[l] = label;
                 }
                 te_sync();
-                run_items(nb, items);
+                const uint32_t o = sOv;
+                run_rows(o & 0xffffu, o >> 16);
+                te_sync();
             }
         }
-        // end of the round; each thread retires its own frontier entries (the
-        // next round's reduction orders this before any other thread's reads)
-        if (open) nlevels += 1;
+        te_sync();
         n_alive -= nF;
         r += 1;
-        open = false;
-        for (uint32_t mm = mask; mm; mm &= mm - 1) sSt[l0 + __builtin_ctz(mm)] = TE_DEAD;
+        pns = ns;
+        pnF = nF;
+        q = qn;
     }
     {
         uint32_t u0, u1, gone = 0;
         (void)te_reduce(R, par, 0u, 0xffffffffu, destroyed, &u0, &u1, &gone);
         mu_alive -= gone;
     }
-    for (int l = t; l < A; l += TE_BLOCK) b.core[glob[l]] = sDeg[l];
+    __syncthreads();   // (the core numbers are read by other threads than wrote them)
+    for (int l = t; l < A; l += BT) {
+        b.core[glob[l]] = core_l[l];
+        b.stamp[glob[l]] = -1;
+    }
     if (t == 0) {
         GraphState &g0 = gs[0];
         g0.k = k;
@@ -2958,11 +2937,8 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tail_engine(PeelBufs b, const int3
         g0.nF[0] = g0.nF[1] = 0;
         g0.nlevels = nlevels;
         g0.sel = 0;
-        c->n_alive = n_alive;
-        c->round = r;
-        c->nF[0] = c->nF[1] = 0;
-        c->nsel[0] = c->nsel[1] = 0;
-        c->pending = 0;
+        // (the caller settles what the graphs share: k_te_close)
+        atomicMax(&c->round, r);
     }
 }
 
@@ -3032,6 +3008,30 @@ __global__ __launch_bounds__(TE_HBLOCK) void k_te_heavy(TeState *ts, const int64
     __syncthreads();
     for (int l = threadIdx.x; l < A; l += TE_HBLOCK)
         if (sLoss[l]) atomicSub(&ts->deg[l], sLoss[l]);
+}
+
+// After the engine: the graphs it took are finished; the others' alive
+// vertices and level openings are counted again.  (A batch with graphs left
+// is at its start: no frontier is pending.)
+__global__ __launch_bounds__(BLOCK) void k_te_close(PeelBufs b, int32_t left) {
+    PeelCtl *c = b.ctl;
+    __shared__ int32_t sSel;
+    if (threadIdx.x == 0) sSel = 0;
+    __syncthreads();
+    int32_t sel = 0;
+    for (int32_t g = threadIdx.x; g < b.G; g += BLOCK) sel += b.gs[g].sel ? 1 : 0;
+    if (sel) atomicAdd(&sSel, sel);
+    __syncthreads();
+    if (threadIdx.x) return;
+    c->n_alive = left;
+    c->nsel[c->cur] = sSel;
+    c->nsel[c->cur ^ 1] = 0;
+    c->pending = 0;
+    if (left) {
+        c->round = 0;                       // (the others' rounds start at 0; the largest round is kept aside)
+    } else {
+        c->nF[0] = c->nF[1] = 0;
+    }
 }
 
 // Times every launch of one kernel: the launch carries a start and a stop
@@ -3139,33 +3139,68 @@ static void launch_peel_items(const PeelBufs &b, hipStream_t s, u64 *gS, int32_t
     }
 }
 
-// The rest of a single graph's h = 3 peel by the tail engine, once at most
-// TE_MAX vertices are alive (the state is between two rounds).  Returns
-// false, having changed nothing, when the degrees could exceed 32 bits or
-// the rewritten rows would not fit; the environment variable
-// DSD_TAIL_ENGINE=0 turns it off.
-static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hipStream_t s, Scratch &sc,
-                        KernelTimes *kt) {
+// The rest of the peel (h = 2, or h = 3 with triangle lists) of every graph
+// with at most TE_MAX vertices alive, by the tail engine.  Between two rounds
+// only if that is every graph left; at the start of a batch the larger ones go
+// on without them.  Returns the vertices left, or -1, having changed nothing,
+// when a graph's degrees could exceed 32 bits, the rewritten rows would not
+// fit, or no graph (or not every one, between rounds) is small enough; the
+// environment variable DSD_TAIL_ENGINE=0 turns it off.  max_round (nullable):
+// the largest round count of the graphs taken.
+static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_start, hipStream_t s, Scratch &sc,
+                           KernelTimes *kt, int32_t *max_round) {
     const char *env = std::getenv("DSD_TAIL_ENGINE");
-    if (env && std::strcmp(env, "0") == 0) return false;
-    if (n_alive < 1 || n_alive > TE_MAX) return false;
-    GraphState g0;
-    DSD_HIP(hipMemcpyAsync(&g0, b.gs, sizeof(GraphState), hipMemcpyDeviceToHost, s));
+    if (env && std::strcmp(env, "0") == 0) return -1;
+    const int32_t n = b.n;
+    if (n_alive < 1) return -1;
+    std::vector<GraphState> gst(b.G);
+    int32_t round0 = 0;
+    DSD_HIP(hipMemcpyAsync(gst.data(), b.gs, (size_t)b.G * sizeof(GraphState), hipMemcpyDeviceToHost, s));
+    if (b.G > 1) DSD_HIP(hipMemcpyAsync(&round0, &b.ctl->round, sizeof(int32_t), hipMemcpyDeviceToHost, s));
     DSD_HIP(hipStreamSynchronize(s));
-    if (g0.mu_alive >= ((u64)1 << 32) || g0.n_alive != n_alive) return false;   // degrees <= mu_alive
+    std::vector<TeGraph> tg[3];                       // by workgroup: up to 2,048, 4,096 and TE_MAX vertices
+    std::vector<int32_t> gbase(b.G, -1);
+    int64_t total_a = 0, seen = 0;
+    u64 mu = 0;
+    for (int32_t g = 0; g < b.G; g++) {
+        const GraphState &st = gst[g];
+        if (st.n_alive <= 0) continue;
+        seen += st.n_alive;
+        if (st.n_alive > TE_MAX || st.mu_alive >= ((u64)1 << 32)) {   // degrees <= mu_alive
+            if (!at_start) return -1;
+            continue;
+        }
+        const int32_t A = (int32_t)st.n_alive;
+        gbase[g] = (int32_t)total_a;
+        tg[A > 1024 * TE_FEW ? 2 : A > 512 * TE_FEW ? 1 : 0].push_back(TeGraph{g, (int32_t)total_a, A});
+        total_a += A;
+        mu += st.mu_alive;
+    }
+    if (total_a == 0 || seen != n_alive || mu >= ((u64)1 << 40)) return -1;
     // every clique of the tail sits in ppc words of the rows (a triangle in
     // its three members' rows, an edge in its two ends'), 4 bytes each
     const int64_t ppc = h == 3 ? 3 : 2;
-    const int64_t bytes = 4 * ppc * (int64_t)g0.mu_alive + 8 * (int64_t)n + 64 * n_alive;
+    const int64_t bytes = 4 * ppc * (int64_t)mu + 8 * (int64_t)n + 64 * total_a;
     const int64_t *roff = h == 3 ? b.tvoff : b.row_ptr;
     const int32_t *rdat = h == 3 ? b.tpairs : b.col;
     size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > (int64_t)(free_b / 4)) return false;
-    const int32_t A = (int32_t)n_alive;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > (int64_t)(free_b / 4)) return -1;
+    const int32_t A = (int32_t)total_a;
     uint32_t *flag = sc.get_n<uint32_t>(n), *loc = sc.get_n<uint32_t>(n);
-    int32_t *glob = sc.get_n<int32_t>(A), *cnt = sc.get_n<int32_t>(2);
+    int32_t *glob = sc.get_n<int32_t>(A), *cnt = sc.get_n<int32_t>(2), *dbase = nullptr;
+    uint32_t *core_l = sc.get_n<uint32_t>(A);
     int64_t *ib = sc.get_n<int64_t>(A + 1);
-    k_te_flags<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(b.stamp, n, b.ctl, flag);
+    std::vector<TeGraph> all(tg[0]);
+    all.insert(all.end(), tg[1].begin(), tg[1].end());
+    all.insert(all.end(), tg[2].begin(), tg[2].end());
+    TeGraph *dtg = nullptr;
+    if (b.G > 1) {
+        dtg = sc.get_n<TeGraph>((int64_t)all.size());
+        dbase = sc.get_n<int32_t>(b.G);
+        DSD_HIP(hipMemcpyAsync(dtg, all.data(), all.size() * sizeof(TeGraph), hipMemcpyHostToDevice, s));
+        DSD_HIP(hipMemcpyAsync(dbase, gbase.data(), (size_t)b.G * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    }
+    k_te_flags<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(b, dbase, flag);
     scan_exclusive_u32(flag, loc, n, s, sc);
     fill_i32((int32_t *)(ib + A), 0, 2, s);
     k_te_glob<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(flag, loc, n, roff, glob, ib, cnt);
@@ -3177,10 +3212,10 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
     const int64_t NI = hv[0];
     if ((int32_t)hv[1] != A) throw Error(-3, "tail engine: the tail's vertex count disagrees with the alive count");
     int64_t *kc = sc.get_n<int64_t>(NI + 1);
-    const int gp = grid_for(NI, WAVES_PER_BLOCK, 8192), gA = grid_for(A, BLOCK, 64);
+    const int gp = grid_for(NI, WAVES_PER_BLOCK, 8192), gA = grid_for(A, BLOCK, 1024);
     if (NI > 0) {
-        if (h == 3) k_te_pairs<false, 3><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, nullptr);
-        else k_te_pairs<false, 2><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, nullptr);
+        if (h == 3) k_te_pairs<false, 3><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, nullptr, b.gid, dbase);
+        else k_te_pairs<false, 2><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, nullptr, b.gid, dbase);
     }
     // rows padded to four pairs, so that lanes load them four at a time
     int64_t *vcnt = sc.get_n<int64_t>(A), *lrow = sc.get_n<int64_t>(A + 1);
@@ -3190,9 +3225,13 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
     int64_t total = 0;
     DSD_HIP(hipMemcpyAsync(&total, lrow + A, sizeof(int64_t), hipMemcpyDeviceToHost, s));
     DSD_HIP(hipStreamSynchronize(s));
-    if (total > ppc * (int64_t)g0.mu_alive + 3 * (int64_t)A)
+    if (total > ppc * (int64_t)mu + 3 * (int64_t)A)
         throw Error(-3, "tail engine: more pairs than the tail's cliques allow");
-    if (total >= ((int64_t)1 << 32)) return false;   // row starts are kept in 32 bits
+    // (a graph's row starts are kept in 32 bits from its first row on)
+    for (const TeGraph &x : all)
+        if (ppc * (int64_t)gst[x.g].mu_alive + 3 * (int64_t)x.A >= ((int64_t)1 << 32)) {
+            if (b.G > 1 || total >= ((int64_t)1 << 32)) return -1;
+        }
     u64 walked = 0;   // pairs the engine walks: every kept pair once
     if (kt) {
         u64 *s2 = sc.get_n<u64>(2);
@@ -3202,37 +3241,49 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
     k_te_ioff<<<gA, BLOCK, 0, s>>>(ib, lrow, A, kc);
     uint32_t *lp = sc.get_n<uint32_t>(total);
     if (NI > 0) {
-        if (h == 3) k_te_pairs<true, 3><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp);
-        else k_te_pairs<true, 2><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp);
+        if (h == 3) k_te_pairs<true, 3><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp, b.gid, dbase);
+        else k_te_pairs<true, 2><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp, b.gid, dbase);
     }
     k_te_pad<<<gA, BLOCK, 0, s>>>(lrow, vcnt, A, lp);
     fill_i32(cnt, 0, 1, s);
-    // the state for grid rounds
-    TeState *ts = sc.get_n<TeState>(1);
+    // the state for grid rounds (a single graph's; in a batch the other graphs keep the CUs busy)
+    TeState *ts = nullptr;
     TeState hts{};
-    hts.deg = sc.get_n<uint32_t>(A);
-    hts.st = sc.get_n<uint8_t>(A);
-    hts.F = sc.get_n<uint32_t>(A);
-    hts.ipre = sc.get_n<uint32_t>(A + 1);
-    hts.imap = sc.get_n<uint32_t>(total / TE_ITEM + A + 1);   // items of one round: sum of ceil(row / TE_ITEM)
-    DSD_HIP(hipMemcpyAsync(ts, &hts, sizeof(TeState), hipMemcpyHostToDevice, s));
+    if (b.G == 1) {
+        ts = sc.get_n<TeState>(1);
+        hts.deg = sc.get_n<uint32_t>(A);
+        hts.st = sc.get_n<uint8_t>(A);
+        hts.F = sc.get_n<uint32_t>(A);
+        hts.ipre = sc.get_n<uint32_t>(A + 1);
+        hts.imap = sc.get_n<uint32_t>(total / TE_ITEM + A + 1);   // items of one round: sum of ceil(row / TE_ITEM)
+        DSD_HIP(hipMemcpyAsync(ts, &hts, sizeof(TeState), hipMemcpyHostToDevice, s));
+    }
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     if (kt && kt->time_main)
         for (auto &e : ev) DSD_HIP(hipEventCreate(&e));
     double engine_ms = 0, grid_ms = 0;
     u64 launches = 0;
     int resume = 0;
-    uint32_t heavy = TE_HEAVY;
-    if (const char *hp = std::getenv("DSD_TE_GRID_PAIRS")) heavy = (uint32_t)std::strtoul(hp, nullptr, 10);
+    uint32_t heavy = b.G == 1 ? TE_HEAVY : 0xffffffffu;
+    if (const char *hp = std::getenv("DSD_TE_GRID_PAIRS"))
+        if (b.G == 1) heavy = (uint32_t)std::strtoul(hp, nullptr, 10);
+    const int n0 = (int)tg[0].size(), n1 = (int)tg[1].size(), n2 = (int)tg[2].size();
     while (true) {
         if (ev[0]) DSD_HIP(hipEventRecord(ev[0], s));
-        if (h == 3) k_tail_engine<3><<<1, TE_BLOCK, 0, s>>>(b, glob, lrow, lp, A, cnt, ts, resume, heavy);
-        else k_tail_engine<2><<<1, TE_BLOCK, 0, s>>>(b, glob, lrow, lp, A, cnt, ts, resume, heavy);
+        // the largest graphs first: they take longest
+        auto run = [&](auto k2, auto k1, auto k0) {
+            const TeGraph *t1 = dtg ? dtg + n0 : nullptr, *t2 = dtg ? t1 + n1 : nullptr;
+            if (n2) k2<<<n2, 1024, 0, s>>>(b, t2, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
+            if (n1) k1<<<n1, 1024, 0, s>>>(b, t1, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
+            if (n0) k0<<<n0, 512, 0, s>>>(b, dtg, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
+        };
+        if (h == 3) run(k_tail_engine<3, 1024, TE_PER>, k_tail_engine<3, 1024, TE_FEW>, k_tail_engine<3, 512, TE_FEW>);
+        else run(k_tail_engine<2, 1024, TE_PER>, k_tail_engine<2, 1024, TE_FEW>, k_tail_engine<2, 512, TE_FEW>);
         DSD_HIP(hipGetLastError());
         if (ev[1]) DSD_HIP(hipEventRecord(ev[1], s));
         launches += 1;
         int32_t err = 0;
-        DSD_HIP(hipMemcpyAsync(&hts, ts, sizeof(TeState), hipMemcpyDeviceToHost, s));
+        if (ts) DSD_HIP(hipMemcpyAsync(&hts, ts, sizeof(TeState), hipMemcpyDeviceToHost, s));
         DSD_HIP(hipMemcpyAsync(&err, cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
         DSD_HIP(hipStreamSynchronize(s));
         if (ev[0]) {
@@ -3245,7 +3296,7 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
                 if (e) (void)hipEventDestroy(e);
             throw Error(-3, "tail engine: a round removed no vertex");
         }
-        if (!hts.heavy) break;
+        if (!ts || !hts.heavy) break;
         // the round the engine stopped at, on every CU; then the engine resumes
         if (ev[2]) DSD_HIP(hipEventRecord(ev[2], s));
         k_te_expand<<<grid_for(hts.nF, WAVES_PER_BLOCK, 1024), BLOCK, 0, s>>>(ts);
@@ -3264,6 +3315,12 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
     }
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
+    if (max_round) {
+        DSD_HIP(hipMemcpyAsync(max_round, &b.ctl->round, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        DSD_HIP(hipStreamSynchronize(s));
+    }
+    const int64_t left = n_alive - total_a;
+    k_te_close<<<1, BLOCK, 0, s>>>(b, (int32_t)left);
     if (kt) {
         kt->tail_ms += engine_ms;
         kt->tail_launches += launches;
@@ -3273,7 +3330,7 @@ static bool tail_engine(const PeelBufs &b, int h, int32_t n, int64_t n_alive, hi
         kt->tail_grid_rounds += hts.rounds;
         kt->tail_grid_pairs += hts.pairs;
     }
-    return true;
+    return left;
 }
 
 PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 mu, u64 k_floor, u64 *core,
@@ -3449,7 +3506,12 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
         compact_adjacency(b, s, sc);
         compacted_at = n_alive;
     }
-    const bool engine = (listed || h == 2) && G == 1 && !min_degree && pattern == 0;
+    const bool engine = (listed || h == 2) && pattern == 0;
+    int32_t early_rounds = 0;   // rounds of the graphs of a batch that the tail engine took at the start
+    if (engine && G > 1 && n_alive > 0) {
+        const int64_t left = tail_engine(b, h, n_alive, true, s, sc, kt, &early_rounds);
+        if (left >= 0) n_alive = left;
+    }
     // DSD_PEEL_GRAPH=1: every round's kernels replayed from a captured HIP
     // graph instead of launched one by one (not with per-launch timing)
     const char *pg = std::getenv("DSD_PEEL_GRAPH");
@@ -3457,7 +3519,9 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     RoundGraphs graphs;
     if (use_graph) DSD_HIP(hipStreamCreateWithFlags(&graphs.cs, hipStreamNonBlocking));
     while (n_alive > 0) {
-        if (engine && n_alive <= TE_MAX && tail_engine(b, h, n, n_alive, s, sc, kt)) break;
+        if (engine && (G == 1 ? n_alive <= TE_MAX : steps > 0 && n_alive < (int64_t)G * TE_MAX) &&
+            tail_engine(b, h, n_alive, false, s, sc, kt, nullptr) == 0)
+            break;
         if (ctail && steps > 0 && clique_tail(b, h, n_alive, s, sc, kt)) break;
         if (compacting && n_alive < compacted_at / 2) {
             compact_adjacency(b, s, sc);
@@ -3583,7 +3647,7 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
         kt->main_entries += fin.work[2];
         kt->main2_words += fin.work[3];
     }
-    res.rounds = fin.round;
+    res.rounds = std::max(fin.round, early_rounds);
     res.graph_levels.resize(G);
     for (int32_t i = 0; i < G; i++) {
         if (gst[i].n_alive != 0) throw Error(-3, "peel ended with alive vertices in a graph");
