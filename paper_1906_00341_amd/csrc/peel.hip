@@ -2361,10 +2361,11 @@ constexpr int TE_MAX = (int)TAIL_ENGINE_VERTICES;   // tail vertices: local ids 
 // above 4,096, 4 a thread up to there, 512 threads up to 2,048 (29 KB of LDS, so
 // the waves a CU holds bound the graphs of a batch on it).
 constexpr int TE_PER = 16, TE_FEW = 4;
-constexpr int TE_PL = 8;                      // consecutive pairs per lane
+constexpr int TE_PL = 4;                      // consecutive pairs per lane
 constexpr int TE_ITEM = WAVE * TE_PL;         // pairs per work item of a round
-constexpr uint32_t TE_SHORT = 8 * TE_PL;      // a row of at most so many pairs is taken by eight lanes
+constexpr uint32_t TE_SHORT = 16 * TE_PL;     // a row of at most so many pairs is taken by 16 lanes
 constexpr int TE_FB = 2048;                   // listed vertices of a frontier (larger ones: in chunks of ids)
+constexpr int TE_LV = 64;                     // level table entries written at a time
 constexpr int TE_CH = 4096;                   // pairs per item of the row rewrite
 constexpr uint32_t TE_NONE = 0xffffffffu;     // padding (local ids are below 2^14)
 constexpr uint8_t TE_DEAD = 0, TE_CUR = 1, TE_ALIVE = 2;
@@ -2576,6 +2577,33 @@ __device__ __forceinline__ uint32_t te_reduce(TeRed<NW> &R, int &par, uint32_t c
     return before + pre;
 }
 
+// minimum of m (*mall) and sum of s (*sall) over the workgroup's NW <= 16 waves, in
+// one exchange; every thread calls it with the same par
+template <int NW>
+__device__ __forceinline__ void te_min_sum(TeRed<NW> &R, int &par, uint32_t m, uint32_t s, uint32_t *mall,
+                                           uint32_t *sall) {
+    static_assert(NW == 8 || NW == 16, "the waves' values are reduced inside a 16-lane row");
+    const uint32_t wmin = te_wave_reduce<true>(m), wsum = __ballot(s != 0) ? te_wave_reduce<false>(s) : 0u;
+    if (lane() == 0) {
+        R.mn[par][threadIdx.x / WAVE] = wmin;
+        R.sum[par][threadIdx.x / WAVE] = wsum;
+    }
+    te_sync();
+    const int w = lane() % 16;
+    uint32_t mi = R.mn[par][w % NW], si = w < NW ? R.sum[par][w % NW] : 0u;
+    mi = te_dpp_op<true>(mi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)mi, 0xb1, 0xf, 0xf, false));
+    si = te_dpp_op<false>(si, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)si, 0xb1, 0xf, 0xf, false));
+    mi = te_dpp_op<true>(mi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)mi, 0x4e, 0xf, 0xf, false));
+    si = te_dpp_op<false>(si, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)si, 0x4e, 0xf, 0xf, false));
+    mi = te_dpp_op<true>(mi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)mi, 0x141, 0xf, 0xf, false));
+    si = te_dpp_op<false>(si, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)si, 0x141, 0xf, 0xf, false));
+    mi = te_dpp_op<true>(mi, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)mi, 0x140, 0xf, 0xf, false));
+    si = te_dpp_op<false>(si, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)si, 0x140, 0xf, 0xf, false));
+    *mall = (uint32_t)__builtin_amdgcn_readfirstlane((int)mi);
+    *sall = (uint32_t)__builtin_amdgcn_readfirstlane((int)si);
+    par ^= 1;
+}
+
 // A vertex's word in LDS: its degree in the low bits (below C(TE_MAX, 2) < 2^27),
 // its state above.  The states are those of round r with q = r mod 3: TQ_IN(q) is
 // the round's frontier, TQ_IN(q + 1) the next round's (still alive), TQ_IN(q - 1)
@@ -2607,32 +2635,37 @@ __device__ __forceinline__ uint32_t te_wave_scan(uint32_t v, uint32_t *total) {
 // round, and that round ends first.  A round whose frontier rows hold more
 // than heavy pairs is left to the grid.
 // A workgroup takes the graph tg[blockIdx.x] (nullptr: the single graph, of A1
-// vertices); heavy is only below 2^32 - 1 for a single graph.  core_l: scratch,
-// the tail vertices' core numbers (min-degree mode: rounds) by local id.
+// vertices); heavy is only below 2^32 - 1 for a single graph.
 //
 // Small graphs and sparse tails are bound by the chain of dependent steps of a
 // round, so there is one barrier a round inside a level.  The thread whose subtraction takes a degree to k or below
 // puts the vertex on the next frontier's list, so only a new level looks all the
-// vertices over.  Rows of at most TE_SHORT pairs are taken by eight lanes each;
+// vertices over.  Rows of at most TE_SHORT pairs are taken by 16 lanes each;
 // longer ones in items of TE_ITEM pairs by whole waves, every wave finding its
-// items in a scan of the listed rows' lengths that it makes for itself.  (With the
-// frontier selected anew each round, by eight reductions over the workgroup and a
-// binary search per item: 375 us for a G(n, p) of 2,000 vertices, h = 2, now 110;
-// 8.3 ms for a power-law graph of 30,011 vertices, h = 3, now 4.5.)  Dense tails
-// are bound by what one CU reads, about 8 B a cycle.
+// items in a scan of the listed rows' lengths that it makes for itself.  No store
+// stands before a row's loads (they would wait for it): core numbers stay in the
+// degree words, level entries in sLv.  Dense tails are bound by the vector units of
+// their one CU, some 27 operations a pair.
+// Measured, against a selection over all vertices each round (eight reductions
+// over the workgroup, a binary search per item): G(n, p) of 2,000 vertices, h = 2,
+// three peels 1.13 -> 0.24 ms; power-law graph of 30,011 vertices, h = 3, 830
+// rounds 8.3 -> 2.8 ms; of 1,000,000 vertices, 5,183 rounds and 56 million pairs
+// 40 -> 32 ms (0.42 ns a pair in its dense rounds).  512 threads instead of 1,024:
+// 3.4 and 39 ms for the two power-law graphs.
 template <int H, int BT, int PER>
 __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *tg, int32_t A1, const int32_t *glob_all,
                                                     const int64_t *lrow_all, const uint32_t *lp_all,
-                                                    uint32_t *core_all, int32_t *err, TeState *ts, int resume,
-                                                    uint32_t heavy, int32_t round0) {
+                                                    int32_t *err, TeState *ts, int resume, uint32_t heavy,
+                                                    int32_t round0) {
     constexpr int TEM = BT * PER, NW = BT / WAVE;
     constexpr uint32_t FB = TEM < TE_FB ? TEM : TE_FB;
     static_assert(FB >= BT, "a chunk of ids has to fit the list");
-    __shared__ __align__(16) uint32_t sDeg[TEM];
+    __shared__ __align__(16) uint32_t sDeg[TEM + WAVE];   // (behind the vertices: a dead slot per lane)
     __shared__ uint32_t sRs[TEM + 1];
     __shared__ uint16_t sF[3][FB];           // a frontier's short rows from the front, its long ones from the back
     __shared__ u64 sCnt[3];
     __shared__ uint32_t sOv;                 // a chunk's short rows | long ones << 16 (frontiers above FB)
+    __shared__ u64 sLv[3][TE_LV];            // level table entries not yet written (no store stands before a row's loads)
     __shared__ TeRed<NW> R;
     PeelCtl *c = b.ctl;
     const TeGraph me = tg ? tg[blockIdx.x] : TeGraph{0, 0, A1};
@@ -2641,7 +2674,6 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
     const int32_t *glob = glob_all + me.base;
     const int64_t *lrow = lrow_all + me.base;
     const uint32_t *lp = lp_all + lrow[0];
-    uint32_t *core_l = core_all + me.base;
     const bool minpeel = b.minpeel != 0;
     const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t / WAVE), L = lane();
     int32_t r, nlevels;
@@ -2659,7 +2691,8 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
         open = gs[0].sel != 0;
     } else {
         // the end of the round the grid processed
-        for (int l = t; l < TEM; l += BT) sDeg[l] = l < A && ts->st[l] == TE_ALIVE ? ts->deg[l] : TQ_DEAD;
+        for (int l = t; l < TEM; l += BT)
+            sDeg[l] = l < A ? ts->deg[l] | (ts->st[l] == TE_ALIVE ? 0u : TQ_DEAD) : TQ_DEAD;
         r = ts->r + 1;
         k = ts->k;
         mu_alive = ts->mu_alive;
@@ -2670,6 +2703,7 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
     }
     for (int l = t; l <= A; l += BT) sRs[l] = (uint32_t)(lrow[l] - lrow[0]);
     if (t < 3) sCnt[t] = 0;
+    if (t < WAVE) sDeg[TEM + t] = TQ_DEAD;
     const int64_t lv_base = gs[0].lv_base;
     int par = 0;
     __syncthreads();
@@ -2677,8 +2711,38 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
     const int l0 = t * PER;
     bool some = true;             // an id of this wave was alive when a level last opened
     int q = 0;                    // the round mod 3
-    uint32_t pns = 0, pnF = 0;    // the last round's short rows and frontier
+    uint32_t pns = 0, pnF = 0, plabel = 0;   // the last round's short rows, frontier and label
     int64_t guard = 0;
+    int lv0 = nlevels;            // the first level whose entry sLv holds
+    // vertex l to the list of the frontier of code TQ_IN(to)
+    auto push = [&](int to, uint32_t l) {
+        const uint32_t len = sRs[l + 1] - sRs[l];
+        const bool lg = len > TE_SHORT;
+        atomicAdd(&sDeg[l], TQ_IN(to));
+        const u64 o = atomicAdd((unsigned long long *)&sCnt[to], (1ull << (lg ? 48 : 32)) + len);
+        const uint32_t ps = tq_short(o), pl = tq_long(o);
+        if (ps + pl < FB) sF[to][lg ? FB - 1 - pl : ps] = (uint16_t)l;
+    };
+    // the last frontier is dead for good: its words keep its core number (min-degree mode: its round).
+    // (From the last wave on: the first ones have the short rows.)
+    auto bury = [&](int qp) {
+        if (pnF <= FB) {
+            for (uint32_t i = BT - 1 - t; i < pnF; i += BT) sDeg[sF[qp][i < pns ? i : FB - 1 - (i - pns)]] = TQ_DEAD | plabel;
+        } else {
+            for (int j = 0; j < PER; j++)
+                if ((sDeg[l0 + j] & ~TQ_DEG) == TQ_IN(qp)) sDeg[l0 + j] = TQ_DEAD | plabel;
+        }
+    };
+    auto flush_levels = [&] {
+        te_sync();
+        for (int i = lv0 + t; i < nlevels; i += BT) {
+            b.lv_k[lv_base + i] = sLv[0][i % TE_LV];
+            b.lv_size[lv_base + i] = sLv[1][i % TE_LV];
+            b.lv_mu[lv_base + i] = sLv[2][i % TE_LV];
+        }
+        lv0 = nlevels;
+        te_sync();
+    };
     for (;;) {
         u64 cn = sCnt[q];
         if (cn == 0) {
@@ -2696,11 +2760,11 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                     d[4 * j + 3] = d4.w;
                 }
 #pragma unroll
-                for (int j = 0; j < PER; j++) mn = min(mn, d[j] <= TQ_DEG ? d[j] : 0xffffffffu);
-                some = __ballot(mn != 0xffffffffu) != 0;
+                for (int j = 0; j < PER; j++) mn = min(mn, d[j]);   // (a vertex that is not alive: above TQ_DEG)
+                some = __ballot(mn <= TQ_DEG) != 0;
             }
-            uint32_t u0, gmin, gone;
-            (void)te_reduce(R, par, 0u, mn, destroyed, &u0, &gmin, &gone);
+            uint32_t gmin, gone;
+            te_min_sum(R, par, mn, destroyed, &gmin, &gone);
             destroyed = 0;
             mu_alive -= gone;
             if (minpeel || (u64)gmin > k) {
@@ -2709,28 +2773,22 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
             }
             const uint32_t top = k < TQ_DEG ? (uint32_t)k : TQ_DEG;
             if (mn <= top) {
+                uint32_t mask = 0;
 #pragma unroll
-                for (int j = 0; j < PER; j++) {
-                    if (d[j] > top) continue;
-                    const uint32_t len = sRs[l0 + j + 1] - sRs[l0 + j];
-                    const bool lg = len > TE_SHORT;
-                    const u64 o = atomicAdd((unsigned long long *)&sCnt[q], (1ull << (lg ? 48 : 32)) + len);
-                    const uint32_t ns = tq_short(o), nl = tq_long(o);
-                    if (ns + nl < FB) sF[q][lg ? FB - 1 - nl : ns] = (uint16_t)(l0 + j);
-                    sDeg[l0 + j] = d[j] | TQ_IN(q);
-                }
+                for (int j = 0; j < PER; j++) mask |= (uint32_t)(d[j] <= top) << j;
+                for (; mask; mask &= mask - 1) push(q, (uint32_t)(l0 + __builtin_ctz(mask)));
             }
             // the level table entry of a new level: the level, |R_k| and mu(R_k)
             // as its first round begins
             if (open) {
                 if (t == 0) {
-                    const int64_t at_l = lv_base + nlevels;
-                    b.lv_k[at_l] = k;
-                    b.lv_size[at_l] = (u64)n_alive;
-                    b.lv_mu[at_l] = mu_alive;
+                    sLv[0][nlevels % TE_LV] = k;
+                    sLv[1][nlevels % TE_LV] = (u64)n_alive;
+                    sLv[2][nlevels % TE_LV] = mu_alive;
                 }
                 nlevels += 1;
                 open = false;
+                if (nlevels - lv0 == TE_LV) flush_levels();
             }
             te_sync();
             cn = sCnt[q];
@@ -2741,11 +2799,12 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
             break;
         }
         const int qn = q == 2 ? 0 : q + 1, qp = q == 0 ? 2 : q - 1;
-        // a vertex's core number (min-degree mode: its round)
         const uint32_t label = minpeel ? (uint32_t)r : (uint32_t)k;
         if (fpairs > heavy) {
             // a heavy round goes to the grid: the frontier with its items'
             // starts, and the whole state, to ts; then the engine stops
+            bury(qp);
+            flush_levels();
             uint32_t mask = 0, own = 0;
             for (int j = 0; j < PER; j++) {
                 if ((sDeg[l0 + j] & ~TQ_DEG) != TQ_IN(q)) continue;
@@ -2759,12 +2818,11 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                 const int l = l0 + __builtin_ctz(mm);
                 ts->F[at] = (uint32_t)l;
                 ts->ipre[at] = run;
-                core_l[l] = label;
                 run += (sRs[l + 1] - sRs[l] + TE_ITEM - 1) / TE_ITEM;
             }
             for (int l = t; l < A; l += BT) {
                 const uint32_t w = sDeg[l], st = w & ~TQ_DEG;
-                ts->deg[l] = w & TQ_DEG;
+                ts->deg[l] = st == TQ_IN(q) ? label : w & TQ_DEG;
                 ts->st[l] = st == 0 ? TE_ALIVE : st == TQ_IN(q) ? TE_CUR : TE_DEAD;
             }
             if (t == 0) {
@@ -2783,25 +2841,11 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
             }
             return;
         }
-        // the last frontier is dead for good, and its count is the next but one's
-        if (t == 0) sCnt[qp] = 0;
-        if (pnF <= FB) {
-            for (uint32_t i = t; i < pnF; i += BT) sDeg[sF[qp][i < pns ? i : FB - 1 - (i - pns)]] = TQ_DEAD;
-        } else {
-            for (int j = 0; j < PER; j++)
-                if ((sDeg[l0 + j] & ~TQ_DEG) == TQ_IN(qp)) sDeg[l0 + j] = TQ_DEAD;
-        }
+        if (t == 0) sCnt[qp] = 0;   // the next round's pushes
+        bury(qp);
         // inside a level, the vertices that fall to k or below join the next frontier
         const uint32_t kx = minpeel || k > TQ_DEG ? TQ_DEG : (uint32_t)k;
-        const uint32_t inn = TQ_IN(qn), cur = TQ_IN(q);
-        auto push = [&](uint32_t l) {
-            const uint32_t len = sRs[l + 1] - sRs[l];
-            const bool lg = len > TE_SHORT;
-            atomicAdd(&sDeg[l], inn);
-            const u64 o = atomicAdd((unsigned long long *)&sCnt[qn], (1ull << (lg ? 48 : 32)) + len);
-            const uint32_t ps = tq_short(o), pl = tq_long(o);
-            if (ps + pl < FB) sF[qn][lg ? FB - 1 - pl : ps] = (uint16_t)l;
-        };
+        const uint32_t alive = 1u | 2u << qn, front = 2u << q;   // by a word's state
         auto fetch = [&](uint32_t q0, uint32_t p1, uint32_t *pv) {
 #pragma unroll
             for (int cq = 0; cq < TE_PL / 4; cq++) {
@@ -2813,44 +2857,55 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                 pv[4 * cq + 3] = w.w;
             }
         };
-        // a lane's TE_PL pairs of v's row
+        // A lane's TE_PL pairs of v's row.  All state lookups go out together, then
+        // all subtractions; no value is looked at before the last one is on its way.
         auto pairs = [&](uint32_t v, const uint32_t *pv) {
             uint32_t da[TE_PL], dx[TE_PL];
 #pragma unroll
             for (int j = 0; j < TE_PL; j++) {
-                const uint32_t qv = pv[j] == TE_NONE ? 0u : pv[j];
-                da[j] = sDeg[qv >> 16] & ~TQ_DEG;
-                if (H == 3) dx[j] = sDeg[qv & 0xffffu] & ~TQ_DEG;
+                da[j] = sDeg[min(pv[j] >> 16, (uint32_t)TEM)];   // (padding: the slot TEM, dead)
+                if (H == 3) dx[j] = sDeg[min(pv[j] & 0xffffu, (uint32_t)TEM)];
             }
             // triangle {v, a, x} costs a and x a clique each: x's loss goes
-            // at once, a's are summed over the lane's run of equal a
+            // at once, a's are summed over the lane's run of equal a.  (A lane
+            // without a loss takes 0 from a slot of its own: no branch, and no
+            // wait for one loss before the next.)
             uint32_t acc = 0, ca[TE_PL], oa[TE_PL], ox[TE_PL];
 #pragma unroll
             for (int j = 0; j < TE_PL; j++) {
                 const uint32_t a = pv[j] >> 16, x = pv[j] & 0xffffu;
-                const bool la = da[j] == 0 || da[j] == inn, lx = H == 2 || dx[j] == 0 || dx[j] == inn;
-                const bool ok = pv[j] != TE_NONE && (la || (da[j] == cur && a > v)) &&
-                                (H == 2 || lx || (dx[j] == cur && x > v));
-                destroyed += ok ? 1u : 0u;
-                ox[j] = 0;
-                if (H == 3 && ok && lx) ox[j] = atomicSub(&sDeg[x], 1u);
-                acc += (ok && la) ? 1u : 0u;
+                const uint32_t sa = da[j] >> TQ_SHIFT;
+                const uint32_t la = __builtin_amdgcn_ubfe(alive, sa, 1);
+                uint32_t ok = la | (__builtin_amdgcn_ubfe(front, sa, 1) & (uint32_t)(a > v)), lx = 0;
+                if (H == 3) {
+                    const uint32_t sx = dx[j] >> TQ_SHIFT;
+                    lx = __builtin_amdgcn_ubfe(alive, sx, 1);
+                    ok &= lx | (__builtin_amdgcn_ubfe(front, sx, 1) & (uint32_t)(x > v));
+                }
+                destroyed += ok;
+                if (H == 3) ox[j] = atomicSub(&sDeg[(ok & lx) ? x : TEM + L], ok & lx);
+                acc += ok & la;
                 const bool last = H == 2 || j == TE_PL - 1 || (pv[j + (j < TE_PL - 1)] >> 16) != a;
                 ca[j] = last ? acc : 0u;
-                oa[j] = 0;
-                if (ca[j]) oa[j] = atomicSub(&sDeg[a], ca[j]);
+                oa[j] = atomicSub(&sDeg[ca[j] ? a : TEM + L], ca[j]);
                 acc = last ? 0u : acc;
             }
+            uint32_t hit = 0;   // taken from above k to k or below: first vertices, then second ones
 #pragma unroll
             for (int j = 0; j < TE_PL; j++) {
-                const uint32_t a = pv[j] >> 16, x = pv[j] & 0xffffu;
-                const uint32_t pa = oa[j] & TQ_DEG;
-                if (H == 3 && (ox[j] & TQ_DEG) == kx + 1) push(x);
-                if (pa > kx && pa - ca[j] <= kx) push(a);
+                hit |= (uint32_t)((oa[j] & TQ_DEG) - kx - 1 < ca[j]) << j;
+                if (H == 3) hit |= (uint32_t)((ox[j] & TQ_DEG) == kx + 1) << (TE_PL + j);
+            }
+            if (hit) {
+#pragma unroll
+                for (int j = 0; j < TE_PL; j++) {
+                    if (hit >> j & 1) push(qn, pv[j] >> 16);
+                    if (H == 3 && (hit >> (TE_PL + j) & 1)) push(qn, pv[j] & 0xffffu);
+                }
             }
         };
         auto run_rows = [&](uint32_t nshort, uint32_t nlong) {
-            // short rows: eight lanes each
+            // short rows: 16 lanes each
             for (uint32_t e = t / (TE_SHORT / TE_PL); e < nshort; e += BT / (TE_SHORT / TE_PL)) {
                 const uint32_t v = sF[q][e], p1 = sRs[v + 1];
                 uint32_t pv[TE_PL];
@@ -2858,7 +2913,7 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                 pairs(v, pv);
             }
             // long rows, 64 at a time: a wave takes items wv, wv + NW, ...; the
-            // next one's pairs are loaded while the current one is processed
+            // next two's pairs are loaded while the current one is processed
             uint32_t first = wv;
             for (uint32_t e0 = 0; e0 < nlong; e0 += WAVE) {
                 const uint32_t e = e0 + L;
@@ -2873,24 +2928,30 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                                         (it - (uint32_t)__builtin_amdgcn_readlane((int)pre, at)) * TE_ITEM;
                     fetch(b0 + (uint32_t)L * TE_PL, (uint32_t)__builtin_amdgcn_readlane((int)p1, at), pv);
                 };
-                uint32_t vi = 0, pv[TE_PL];
+                uint32_t v0 = 0, v1 = 0, pv[TE_PL], pn[TE_PL];
+#pragma unroll
+                for (int j = 0; j < TE_PL; j++) pn[j] = TE_NONE;
                 uint32_t it = first;
-                if (it < items) get(it, &vi, pv);
+                if (it < items) get(it, &v0, pv);
+                if (it + NW < items) get(it + NW, &v1, pn);
                 for (; it < items; it += NW) {
-                    uint32_t vn = 0, pn[TE_PL];
+                    uint32_t v2 = 0, pm[TE_PL];
 #pragma unroll
-                    for (int j = 0; j < TE_PL; j++) pn[j] = TE_NONE;
-                    if (it + NW < items) get(it + NW, &vn, pn);
-                    pairs(vi, pv);
-                    vi = vn;
+                    for (int j = 0; j < TE_PL; j++) pm[j] = TE_NONE;
+                    if (it + 2 * NW < items) get(it + 2 * NW, &v2, pm);
+                    pairs(v0, pv);
+                    v0 = v1;
+                    v1 = v2;
 #pragma unroll
-                    for (int j = 0; j < TE_PL; j++) pv[j] = pn[j];
+                    for (int j = 0; j < TE_PL; j++) {
+                        pv[j] = pn[j];
+                        pn[j] = pm[j];
+                    }
                 }
                 first = it - items;   // the next rows go on with the next wave
             }
         };
         if (nF <= FB) {
-            for (uint32_t i = t; i < nF; i += BT) core_l[sF[q][i < ns ? i : FB - 1 - (i - ns)]] = label;
             run_rows(ns, nl);
         } else {
             // a frontier that the list does not hold, BT ids at a time
@@ -2898,11 +2959,10 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
                 if (t == 0) sOv = 0;
                 te_sync();
                 const uint32_t l = (uint32_t)(j * BT + t);
-                if ((sDeg[l] & ~TQ_DEG) == cur) {
+                if ((sDeg[l] & ~TQ_DEG) == TQ_IN(q)) {
                     const bool lg = sRs[l + 1] - sRs[l] > TE_SHORT;
                     const uint32_t o = atomicAdd(&sOv, lg ? 0x10000u : 1u);
                     sF[q][lg ? FB - 1 - (o >> 16) : (o & 0xffffu)] = (uint16_t)l;
-                    core_l[l] = label;
                 }
                 te_sync();
                 const uint32_t o = sOv;
@@ -2915,6 +2975,7 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
         r += 1;
         pns = ns;
         pnF = nF;
+        plabel = label;
         q = qn;
     }
     {
@@ -2922,9 +2983,10 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
         (void)te_reduce(R, par, 0u, 0xffffffffu, destroyed, &u0, &u1, &gone);
         mu_alive -= gone;
     }
-    __syncthreads();   // (the core numbers are read by other threads than wrote them)
+    bury(q == 0 ? 2 : q - 1);
+    flush_levels();
     for (int l = t; l < A; l += BT) {
-        b.core[glob[l]] = core_l[l];
+        b.core[glob[l]] = sDeg[l] & TQ_DEG;
         b.stamp[glob[l]] = -1;
     }
     if (t == 0) {
@@ -3166,7 +3228,8 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         const GraphState &st = gst[g];
         if (st.n_alive <= 0) continue;
         seen += st.n_alive;
-        if (st.n_alive > TE_MAX || st.mu_alive >= ((u64)1 << 32)) {   // degrees <= mu_alive
+        // (a degree is below C(TE_MAX, 2), the level fits beside a vertex's state)
+        if (st.n_alive > TE_MAX || st.mu_alive >= ((u64)1 << 32) || st.k >= ((u64)1 << TQ_SHIFT)) {
             if (!at_start) return -1;
             continue;
         }
@@ -3188,7 +3251,6 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
     const int32_t A = (int32_t)total_a;
     uint32_t *flag = sc.get_n<uint32_t>(n), *loc = sc.get_n<uint32_t>(n);
     int32_t *glob = sc.get_n<int32_t>(A), *cnt = sc.get_n<int32_t>(2), *dbase = nullptr;
-    uint32_t *core_l = sc.get_n<uint32_t>(A);
     int64_t *ib = sc.get_n<int64_t>(A + 1);
     std::vector<TeGraph> all(tg[0]);
     all.insert(all.end(), tg[1].begin(), tg[1].end());
@@ -3273,9 +3335,9 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         // the largest graphs first: they take longest
         auto run = [&](auto k2, auto k1, auto k0) {
             const TeGraph *t1 = dtg ? dtg + n0 : nullptr, *t2 = dtg ? t1 + n1 : nullptr;
-            if (n2) k2<<<n2, 1024, 0, s>>>(b, t2, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
-            if (n1) k1<<<n1, 1024, 0, s>>>(b, t1, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
-            if (n0) k0<<<n0, 512, 0, s>>>(b, dtg, A, glob, lrow, lp, core_l, cnt, ts, resume, heavy, round0);
+            if (n2) k2<<<n2, 1024, 0, s>>>(b, t2, A, glob, lrow, lp, cnt, ts, resume, heavy, round0);
+            if (n1) k1<<<n1, 1024, 0, s>>>(b, t1, A, glob, lrow, lp, cnt, ts, resume, heavy, round0);
+            if (n0) k0<<<n0, 512, 0, s>>>(b, dtg, A, glob, lrow, lp, cnt, ts, resume, heavy, round0);
         };
         if (h == 3) run(k_tail_engine<3, 1024, TE_PER>, k_tail_engine<3, 1024, TE_FEW>, k_tail_engine<3, 512, TE_FEW>);
         else run(k_tail_engine<2, 1024, TE_PER>, k_tail_engine<2, 1024, TE_FEW>, k_tail_engine<2, 512, TE_FEW>);
