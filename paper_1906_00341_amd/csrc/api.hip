@@ -92,13 +92,14 @@ void end_stats(dsd_graph_s *G, const KernelTimes &kt) {
 // clique-degrees (rank space) and mu; throws on overflow
 u64 degrees_and_mu(dsd_graph_s *G, int h, const uint8_t *mask, u64 *deg, KernelTimes *kt) {
     hipStream_t s = G->stream;
-    if (!clique_degrees(G->g, h, mask, deg, s, G->sc, kt))
+    EventSpan span;
+    if (!clique_degrees(G->g, h, mask, deg, s, G->sc, kt, 512, &span))
         throw Error(DSD_EOVERFLOW, "clique counts could exceed 64 bits");
     u64 *sum = G->sc.get_n<u64>(2);
     sum_u64_128(deg, G->g.n, sum, s, G->sc);
     u64 hs[2];
-    DSD_HIP(hipMemcpyAsync(hs, sum, sizeof(hs), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(G->sc).add(hs, sum, 2).run(s);
+    if (kt) kt->k3_ms += span.ms();
     if (hs[1] != 0) throw Error(DSD_EOVERFLOW, "sum of clique-degrees exceeds 64 bits");
     if (hs[0] % (u64)h != 0) throw Error(DSD_EDEVICE, "clique-degree sum not divisible by h");
     return hs[0] / (u64)h;
@@ -649,12 +650,10 @@ u64 core_app_run(dsd_graph_s *G, int h, uint8_t *best, dsd_rational *density) {
         fill_i32(cnt, 0, 1, s);
         k_count_top<<<grid_for(n, BLOCK, 2048), BLOCK, 0, s>>>(keys, n, G->g.bits, cnt);
         int32_t ntop = 0;
-        DSD_HIP(hipMemcpyAsync(&ntop, cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
+        Readback(G->sc).add(&ntop, cnt).run(s);
         auto gamma_at = [&](int64_t i) -> u64 {
             u64 k = 0;
-            DSD_HIP(hipMemcpyAsync(&k, keys + i, sizeof(u64), hipMemcpyDeviceToHost, s));
-            DSD_HIP(hipStreamSynchronize(s));
+            Readback(G->sc).add(&k, keys + i).run(s);
             return binom_sat(keymax - (k >> G->g.bits), h - 1);
         };
         int64_t w = std::min<int64_t>(n, std::max<int64_t>(64, ntop));
@@ -667,8 +666,7 @@ u64 core_app_run(dsd_graph_s *G, int h, uint8_t *best, dsd_rational *density) {
             G->stats.t_enum_ms += te.stop();
             masked_min_u64(d, inW, n, mn, s);
             u64 kl = 0;
-            DSD_HIP(hipMemcpyAsync(&kl, mn, sizeof(u64), hipMemcpyDeviceToHost, s));
-            DSD_HIP(hipStreamSynchronize(s));
+            Readback(G->sc).add(&kl, mn).run(s);
             const u64 k0 = std::max(kl, kmax);
             // G[W]'s k_max is at least its density mu(W)/|W| (its densest
             // subgraph lies in the ceil(rho)-core, Lemma 7), so the levels

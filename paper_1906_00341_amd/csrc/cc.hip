@@ -214,22 +214,17 @@ void extract_induced(const DevGraph &g, const uint8_t *mask, const int32_t *labe
     scan_exclusive_i64(pos, pos, n, s, sc);
     int64_t last = 0;
     uint8_t lastm = 0;
-    DSD_HIP(hipMemcpyAsync(&last, pos + n - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(&lastm, mask + n - 1, 1, hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&last, pos + n - 1).add(&lastm, mask + n - 1).run(s);
     const int64_t cnt = last + (lastm ? 1 : 0);
     if (cnt == 0) return;
     int32_t *verts = sc.get_n<int32_t>(cnt);
-    int64_t *loff = sc.get_n<int64_t>(cnt);
+    int64_t *loff = sc.get_n<int64_t>(cnt + 1);
     k_compact_verts<<<grid_for(n, BLOCK, 8192), BLOCK, 0, s>>>(mask, pos, n, verts);
     k_local_deg<<<grid_for(cnt, WAVES_PER_BLOCK, 8192), BLOCK, 0, s>>>(verts, cnt, g.row_ptr, g.col, mask, loff);
-    int64_t lastdeg = 0;
-    DSD_HIP(hipMemcpyAsync(&lastdeg, loff + cnt - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    scan_exclusive_i64(loff, loff, cnt, s, sc);
-    int64_t lastoff = 0;
-    DSD_HIP(hipMemcpyAsync(&lastoff, loff + cnt - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
-    const int64_t tot = lastoff + lastdeg;
+    fill_u64((u64 *)(loff + cnt), 0, 1, s);
+    scan_exclusive_i64(loff, loff, cnt + 1, s, sc);
+    int64_t tot = 0;
+    Readback(sc).add(&tot, loff + cnt).run(s);
     int32_t *ladj = sc.get_n<int32_t>(tot);
     u64 *ocore = sc.get_n<u64>(cnt);
     int32_t *olabel = sc.get_n<int32_t>(cnt);
@@ -241,12 +236,13 @@ void extract_induced(const DevGraph &g, const uint8_t *mask, const int32_t *labe
     out.adj.resize(tot);
     out.core.resize(cnt);
     out.label.resize(cnt);
-    DSD_HIP(hipMemcpyAsync(out.rank.data(), verts, cnt * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(out.off.data(), loff, cnt * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    if (tot) DSD_HIP(hipMemcpyAsync(out.adj.data(), ladj, tot * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(out.core.data(), ocore, cnt * sizeof(u64), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(out.label.data(), olabel, cnt * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc)
+        .add(out.rank.data(), verts, cnt)
+        .add(out.off.data(), loff, cnt)
+        .add(out.adj.data(), ladj, tot)
+        .add((u64 *)out.core.data(), ocore, cnt)
+        .add(out.label.data(), olabel, cnt)
+        .run(s);
     out.off[cnt] = tot;
 }
 
@@ -271,15 +267,11 @@ void collect_components(const int32_t *label, const u64 *size, const u64 *dsum, 
     fill_i32(cnt, 0, 1, s);
     k_collect_roots<<<grid_for(n, BLOCK, 8192), BLOCK, 0, s>>>(label, size, dsum, n, cnt, root, osize, odsum);
     int32_t hc = 0;
-    DSD_HIP(hipMemcpyAsync(&hc, cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&hc, cnt).run(s);
     std::vector<int32_t> r(hc);
     std::vector<u64> a(hc), b(hc);
     if (hc) {
-        DSD_HIP(hipMemcpyAsync(r.data(), root, hc * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(a.data(), osize, hc * sizeof(u64), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(b.data(), odsum, hc * sizeof(u64), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
+        Readback(sc).add(r.data(), root, hc).add(a.data(), osize, hc).add(b.data(), odsum, hc).run(s);
     }
     out.resize(hc);
     for (int32_t i = 0; i < hc; i++) out[i] = CompInfo{r[i], a[i], b[i]};

@@ -227,12 +227,11 @@ void build_graph(int32_t n, int64_t P, const int32_t *src, const int32_t *dst, D
         scan_exclusive_i64(pos, pos, P, s, sc);
         int64_t last_pos = 0;
         u64 last_key = 0, prev_key = 0;
-        DSD_HIP(hipMemcpyAsync(&last_pos, pos + P - 1, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(&last_key, keys + P - 1, sizeof(u64), hipMemcpyDeviceToHost, s));
-        if (P > 1) DSD_HIP(hipMemcpyAsync(&prev_key, keys + P - 2, sizeof(u64), hipMemcpyDeviceToHost, s));
         int32_t bad = 0;
-        DSD_HIP(hipMemcpyAsync(&bad, d_bad, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
+        Readback rb(sc);
+        rb.add(&last_pos, pos + P - 1).add(&last_key, keys + P - 1).add(&bad, d_bad);
+        if (P > 1) rb.add(&prev_key, keys + P - 2);
+        rb.run(s);
         if (bad) throw Error(-1, "vertex id outside [0, n)");
         m = last_pos + ((last_key != invalid && (P == 1 || prev_key != last_key)) ? 1 : 0);
         edges = tmp;   // reuse: unique keys
@@ -295,9 +294,7 @@ void build_graph(int32_t n, int64_t P, const int32_t *src, const int32_t *dst, D
     DSD_HIP(hipEventRecord(e1, s));
     int32_t hm[2] = {0, 0};
     u64 hw[2] = {0, 0};
-    DSD_HIP(hipMemcpyAsync(hm, maxes, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(hw, wed, 2 * sizeof(u64), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(hm, maxes, 2).add(hw, wed, 2).run(s);
     g.w2 = hw[0];
     g.s2 = hw[1];
     g.maxdeg = hm[0];

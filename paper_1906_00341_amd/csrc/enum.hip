@@ -85,37 +85,76 @@ __device__ __forceinline__ int root_bin(int d, int R) {
 
 __device__ __forceinline__ u64 sat_add(u64 a, u64 b) { return (a + b < a) ? ~0ull : a + b; }
 
-// pass 0: per-class counts and a saturating bound sum_r C(d+(r), R) on the
-// number of cliques; pass 1: fill the class lists.  Wave-aggregated atomics.
-__global__ void k_classify(const int64_t *row_ptr, const int64_t *dag_off, const uint8_t *mask, int32_t n, int R,
-                           int pass, int32_t *cursor, int32_t *lists, const int32_t *class_off, u64 *bound) {
-    u64 b = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t start = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    const int64_t lim = ((int64_t)n + WAVE - 1) / WAVE * WAVE;   // whole waves stay in the loop
-    for (int64_t r = start; r < lim + stride; r += stride) {
-        if (r - threadIdx.x % WAVE >= lim) break;                    // wave-uniform exit
-        int c = -1, d = 0;
+// clears what a call counts into: the degrees, the bins' two counters and the bound
+__global__ void k_enum_init(u64 *deg, int64_t n, int32_t *cursor, u64 *bound) {
+    const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * blockDim.x) deg[i] = 0;
+    if (i0 < 2 * NBIN) cursor[i0] = 0;
+    if (i0 == 0) *bound = 0;
+}
+
+struct RootOffsets {
+    int32_t off[NBIN + 1];
+};
+constexpr int CLASSIFY_PER = 16;                          // roots per thread
+constexpr int CLASSIFY_TILE = BLOCK * CLASSIFY_PER;       // consecutive roots per workgroup
+
+// FILL false: per-bin counts and a saturating bound sum_r C(d+(r), R) on the
+// number of cliques; FILL true: the bins' lists, from off on.  The bins are
+// counted in LDS, so that a workgroup pays one global atomic per bin for its
+// 4,096 roots (one per bin and wave: 0.31 ms each pass for 2^22 roots).
+template <bool FILL>
+__global__ __launch_bounds__(BLOCK) void k_classify(const int64_t *row_ptr, const int64_t *dag_off, const uint8_t *mask,
+                                                    int32_t n, int R, int32_t *cursor, int32_t *lists, RootOffsets off,
+                                                    u64 *bound) {
+    __shared__ int32_t sCnt[NBIN];
+    __shared__ u64 sBound[WAVES_PER_BLOCK];
+    static_assert(NBIN <= 15, "a bin has to fit four bits");
+    if (threadIdx.x < NBIN) sCnt[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * CLASSIFY_TILE + threadIdx.x;
+    u64 b = 0, bins = 0;   // a thread's bins, four bits each (15: no root)
+#pragma unroll 4
+    for (int j = 0; j < CLASSIFY_PER; j++) {
+        const int64_t r = r0 + (int64_t)j * BLOCK;
+        int c = -1;
         if (r < n && (!mask || mask[r])) {
-            d = (int)(row_ptr[r + 1] - dag_off[r]);
+            const int d = (int)(row_ptr[r + 1] - dag_off[r]);
             c = root_bin(d, R);
+            if (!FILL && c >= 0) b = sat_add(b, binom_sat_dev((u64)d, R));
         }
-        if (pass == 0 && c >= 0) b = sat_add(b, binom_sat_dev((u64)d, R));
+        bins |= (u64)(c & 15) << (4 * j);
         for (int k = 0; k < NBIN; k++) {
-            u64 m = __ballot(c == k);
-            if (!m) continue;
-            int leader = __builtin_ctzll(m);
-            int32_t basepos = 0;
-            if (lane() == leader) basepos = atomicAdd(&cursor[k], __popcll(m));
-            basepos = __shfl(basepos, leader, WAVE);
-            if (pass == 1 && c == k) lists[class_off[k] + basepos + __popcll(m & lanemask_lt())] = (int32_t)r;
+            const u64 m = __ballot(c == k);
+            if (m && lane() == 0) atomicAdd(&sCnt[k], __popcll(m));
         }
     }
-    if (pass == 0) {
+    if (!FILL) {
         for (int d = WAVE / 2; d > 0; d >>= 1) b = sat_add(b, __shfl_xor(b, d, WAVE));
-        if (lane() == 0 && b) {
-            u64 old = atomicAdd(bound, b);
+        if (lane() == 0) sBound[threadIdx.x / WAVE] = b;
+    }
+    __syncthreads();
+    if (threadIdx.x < NBIN && sCnt[threadIdx.x])
+        sCnt[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], sCnt[threadIdx.x]);
+    if (!FILL) {
+        if (threadIdx.x) return;
+        for (int w = 1; w < WAVES_PER_BLOCK; w++) b = sat_add(b, sBound[w]);
+        if (b) {
+            const u64 old = atomicAdd(bound, b);
             if (old + b < old) atomicExch(bound, ~0ull);
+        }
+        return;
+    }
+    __syncthreads();
+    for (int j = 0; j < CLASSIFY_PER; j++) {
+        const int c = (int)(bins >> (4 * j) & 15);
+        for (int k = 0; k < NBIN; k++) {
+            const u64 m = __ballot(c == k);
+            if (!m) continue;
+            int32_t base = 0;
+            if (lane() == 0) base = atomicAdd(&sCnt[k], __popcll(m));
+            base = __shfl(base, 0, WAVE);
+            if (c == k) lists[off.off[k] + base + __popcll(m & lanemask_lt())] = (int32_t)(r0 + (int64_t)j * BLOCK);
         }
     }
 }
@@ -381,41 +420,37 @@ static void launch_one_class(int R, int c, int cap, const DevGraph &g, const Enu
     }
 }
 
-// roots binned by class (rank order kept within a class); false if the
-// counts could overflow 64 bits.  The host copy of off must outlive the
-// stream's use of d_off (the callers synchronise before returning).
+// roots binned by class, deg (length n) cleared; false if the counts could
+// overflow 64 bits
 struct RootClasses {
     int32_t hc[NBIN];
     int32_t off[NBIN + 1];
     int32_t *lists = nullptr;
 };
-static bool classify_roots(const DevGraph &g, int h, const uint8_t *mask, hipStream_t s, Scratch &sc, RootClasses &rc) {
+static bool classify_roots(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hipStream_t s, Scratch &sc,
+                           RootClasses &rc) {
     const int32_t n = g.n;
     const int R = h - 1;
-    int32_t *cursor = sc.get_n<int32_t>(NBIN);
+    int32_t *cursor = sc.get_n<int32_t>(2 * NBIN);
     u64 *bound = sc.get_n<u64>(1);
-    fill_i32(cursor, 0, NBIN, s);
-    fill_u64(bound, 0, 1, s);
-    int blocks = grid_for(n, BLOCK, 4096);
-    k_classify<<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, 0, cursor, nullptr, nullptr, bound);
+    k_enum_init<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(deg, n, cursor, bound);
+    const int blocks = (int)(((int64_t)n + CLASSIFY_TILE - 1) / CLASSIFY_TILE);
+    RootOffsets ro{};
+    k_classify<false><<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, cursor, nullptr, ro, bound);
     u64 hb = 0;
-    DSD_HIP(hipMemcpyAsync(rc.hc, cursor, sizeof(rc.hc), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(&hb, bound, sizeof(u64), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(rc.hc, cursor, NBIN).add(&hb, bound).run(s);
     if (hb == ~0ull || hb > ~0ull / (u64)h) return false;          // counts could overflow 64 bits
     if (rc.hc[7]) throw Error(-5, "an out-neighbourhood exceeds 2048 vertices (limit of the bitmap kernels, h >= 4)");
     rc.off[0] = 0;
     for (int c = 0; c < NBIN; c++) rc.off[c + 1] = rc.off[c] + rc.hc[c];
+    for (int c = 0; c <= NBIN; c++) ro.off[c] = rc.off[c];
     rc.lists = sc.get_n<int32_t>(rc.off[NBIN]);
-    int32_t *d_off = sc.get_n<int32_t>(NBIN + 1);
-    DSD_HIP(hipMemcpyAsync(d_off, rc.off, sizeof(rc.off), hipMemcpyHostToDevice, s));
-    fill_i32(cursor, 0, NBIN, s);
-    k_classify<<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, 1, cursor, rc.lists, d_off, bound);
+    k_classify<true><<<blocks, BLOCK, 0, s>>>(g.row_ptr, g.dag_off, mask, n, R, cursor + NBIN, rc.lists, ro, bound);
     return true;
 }
 
 bool clique_degrees(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hipStream_t s, Scratch &sc,
-                    KernelTimes *kt, int gs_blocks) {
+                    KernelTimes *kt, int gs_blocks, EventSpan *span) {
     const int32_t n = g.n;
     if (n == 0) return true;
     if (h == 2) {
@@ -424,16 +459,11 @@ bool clique_degrees(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hip
         return true;
     }
     const int R = h - 1;
-    fill_u64(deg, 0, n, s);
     RootClasses rc;
-    if (!classify_roots(g, h, mask, s, sc, rc)) return false;
+    if (!classify_roots(g, h, mask, deg, s, sc, rc)) return false;
     EnumCtx ctx{nullptr, mask, deg};
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (kt) {
-        DSD_HIP(hipEventCreate(&e0));
-        DSD_HIP(hipEventCreate(&e1));
-        DSD_HIP(hipEventRecord(e0, s));
-    }
+    EventSpan own, &es = span ? *span : own;
+    if (kt) es.begin(s);
     switch (R) {
         case 2: launch_engine<2>(g, ctx, rc.lists, rc.off, rc.hc, s, sc, gs_blocks); break;
         case 3: launch_engine<3>(g, ctx, rc.lists, rc.off, rc.hc, s, sc, gs_blocks); break;
@@ -442,17 +472,13 @@ bool clique_degrees(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hip
         default: throw Error(-1, "h outside [2, 6]");
     }
     if (kt) {
-        DSD_HIP(hipEventRecord(e1, s));
-        DSD_HIP(hipEventSynchronize(e1));
-        float ms = 0;
-        DSD_HIP(hipEventElapsedTime(&ms, e0, e1));
-        kt->k3_ms += ms;
+        es.end(s);
         for (int c = 0; c < nclass_of(R); c++) kt->k3_launches += class_roots(R, c, rc.hc) ? 1 : 0;
-        (void)hipEventDestroy(e0);
-        (void)hipEventDestroy(e1);
+        if (!span) {
+            DSD_HIP(hipStreamSynchronize(s));
+            kt->k3_ms += own.ms();
+        }
     }
-    // the host copy of `off` must outlive the async H2D copy above
-    DSD_HIP(hipStreamSynchronize(s));
     return true;
 }
 
@@ -463,9 +489,8 @@ std::vector<TuneResult> autotune(const DevGraph &g, int h, hipStream_t s, Scratc
     if (n == 0) return out;
     const int R = h - 1;
     RootClasses rc;
-    if (!classify_roots(g, h, nullptr, s, sc, rc)) throw Error(-4, "clique counts could exceed 64 bits");
     u64 *deg = sc.get_n<u64>(n);
-    fill_u64(deg, 0, n, s);
+    if (!classify_roots(g, h, nullptr, deg, s, sc, rc)) throw Error(-4, "clique counts could exceed 64 bits");
     EnumCtx ctx{nullptr, nullptr, deg};
     DSD_HIP(hipStreamSynchronize(s));
     hipEvent_t e0, e1;

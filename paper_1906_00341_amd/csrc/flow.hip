@@ -719,7 +719,6 @@ struct GpuFlow::Impl {
     int *eu = nullptr, *ev = nullptr, *fwd = nullptr;
     uint8_t *cls = nullptr;
     int64_t *deg = nullptr;
-    int *pinned = nullptr;   // the thread's pinned buffer
     int nv = 0;
     ~Impl() {
         if (s) (void)hipStreamSynchronize(s);
@@ -902,7 +901,6 @@ void GpuFlow::Impl::residual(int n) {
     if (b.nbig > 0)
         DSD_HIP(hipMemcpyAsync(d_big, big.data(), big.size() * sizeof(int), hipMemcpyHostToDevice, I.s));
     b.big = d_big;
-    I.pinned = (int *)thread_pinned();
     DSD_HIP(hipStreamSynchronize(I.s));
 }
 
@@ -923,10 +921,9 @@ int GpuFlow::Impl::global_relabel() {
             cur ^= 1;
             level++;
         }
-        DSD_HIP(hipMemcpyAsync(pinned, b.nfront + cur, sizeof(int), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(pinned + 1, b.nbfront + cur, sizeof(int), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
-        if ((pinned[0] == 0 && pinned[1] == 0) || level > b.n) break;
+        int left[2];
+        Readback(sc).add(&left[0], b.nfront + cur).add(&left[1], b.nbfront + cur).run(s);
+        if ((left[0] == 0 && left[1] == 0) || level > b.n) break;
     }
     return level;
 }
@@ -969,9 +966,9 @@ int64_t GpuFlow::maxflow(const FlowTest &test, std::vector<char> &reach_t, int64
         passes += 8;
         since_relabel += 8;
         // converged when no node was active after the last pass's pushes
-        DSD_HIP(hipMemcpyAsync(I.pinned, b.nact, 2 * sizeof(int), hipMemcpyDeviceToHost, I.s));
-        DSD_HIP(hipStreamSynchronize(I.s));
-        if (I.pinned[0] + I.pinned[1] == 0) {
+        int left[2];
+        Readback(I.sc).add(left, b.nact, 2).run(I.s);
+        if (left[0] + left[1] == 0) {
             *converged = true;
             break;
         }

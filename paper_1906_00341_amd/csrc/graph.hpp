@@ -30,6 +30,36 @@ struct DevGraph {
     bool owned = true;   // the arrays were hipMalloc'd (else they live in a handle's scratch)
 };
 
+// two HIP events around a piece of a stream; ms() once the stream has passed both
+class EventSpan {
+public:
+    EventSpan() = default;
+    EventSpan(const EventSpan &) = delete;
+    EventSpan &operator=(const EventSpan &) = delete;
+    ~EventSpan() {
+        if (a_) (void)hipEventDestroy(a_);
+        if (b_) (void)hipEventDestroy(b_);
+    }
+    void begin(hipStream_t s) {
+        DSD_HIP(hipEventCreate(&a_));
+        DSD_HIP(hipEventCreate(&b_));
+        DSD_HIP(hipEventRecord(a_, s));
+    }
+    void end(hipStream_t s) {
+        DSD_HIP(hipEventRecord(b_, s));
+        ended_ = true;
+    }
+    double ms() const {
+        float t = 0;
+        if (ended_) DSD_HIP(hipEventElapsedTime(&t, a_, b_));
+        return t;
+    }
+
+private:
+    hipEvent_t a_ = nullptr, b_ = nullptr;
+    bool ended_ = false;
+};
+
 // HIP-event timing of the two kernel families, accumulated per call
 struct KernelTimes {
     double k3_ms = 0, k4_ms = 0;
@@ -71,9 +101,10 @@ void free_graph(DevGraph &g);
 // subgraph induced by mask (mask == nullptr: whole graph).  deg is
 // overwritten.  Returns false if the counts could overflow 64 bits.
 // gs_blocks caps the grid of the class whose bitmaps live in global scratch
-// (gs_blocks * 1280 * 20 words of sc).
+// (gs_blocks * 1280 * 20 words of sc).  span (with kt): takes the kernels' time
+// for the caller to read once the stream has drained; without it the call waits.
 bool clique_degrees(const DevGraph &g, int h, const uint8_t *mask, u64 *deg, hipStream_t s, Scratch &sc,
-                    KernelTimes *kt = nullptr, int gs_blocks = 512);
+                    KernelTimes *kt = nullptr, int gs_blocks = 512, EventSpan *span = nullptr);
 
 // ---- launch-grid tuning of the clique enumeration ----
 // One class's measurement: its roots, the default and the chosen grid cap

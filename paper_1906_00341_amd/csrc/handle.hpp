@@ -2,6 +2,7 @@
 // single-graph entry points, the batch and the server.
 #pragma once
 
+#include <chrono>
 #include <hip/hip_runtime.h>
 
 #include <string>
@@ -75,25 +76,14 @@ dsd_status fail(int st, const std::string &msg);
         return dsd::fail(DSD_EDEVICE, e.what());                          \
     }
 
-// HIP-event timer on one stream
+// wall time of a stage: from its start to the stream's end of it
 struct Timer {
     hipStream_t s;
-    hipEvent_t a, b;
-    explicit Timer(hipStream_t st) : s(st) {
-        DSD_HIP(hipEventCreate(&a));
-        DSD_HIP(hipEventCreate(&b));
-        DSD_HIP(hipEventRecord(a, s));
-    }
+    std::chrono::steady_clock::time_point a = std::chrono::steady_clock::now();
+    explicit Timer(hipStream_t st) : s(st) {}
     double stop() {
-        DSD_HIP(hipEventRecord(b, s));
-        DSD_HIP(hipEventSynchronize(b));
-        float ms = 0;
-        DSD_HIP(hipEventElapsedTime(&ms, a, b));
-        return ms;
-    }
-    ~Timer() {
-        (void)hipEventDestroy(a);
-        (void)hipEventDestroy(b);
+        DSD_HIP(hipStreamSynchronize(s));
+        return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - a).count();
     }
 };
 

@@ -2244,8 +2244,7 @@ static void compact_adjacency(PeelBufs &b, hipStream_t s, Scratch &sc) {
     scan_exclusive_i64(cnt, nrow, n, s, sc);
     k_last_row<<<1, 1, 0, s>>>(nrow, cnt, n);
     int64_t total = 0;
-    DSD_HIP(hipMemcpyAsync(&total, nrow + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&total, nrow + n).run(s);
     int32_t *ncol = sc.get_n<int32_t>(total);
     int64_t *ndag = sc.get_n<int64_t>(n);
     k_compact_dag<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(nrow, cnt_out, n, ndag);
@@ -2272,8 +2271,7 @@ static int64_t loop_tables(const DevGraph &g, int *groups, hipStream_t s, Scratc
     fill_u64((u64 *)mx, 0, 1, s);
     if (g.n > 0) k_loop_bound<<<grid_for(g.n, WAVES_PER_BLOCK, 8192), BLOCK, 0, s>>>(g.row_ptr, g.col, g.n, mx);
     unsigned long long bound = 0;
-    DSD_HIP(hipMemcpyAsync(&bound, mx, sizeof(bound), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&bound, mx).run(s);
     int64_t size = 2;
     while (size < 2 * (int64_t)bound) size <<= 1;
     if (size > LOOP_MAX_SLOTS)
@@ -2411,14 +2409,17 @@ __global__ void k_te_flags(PeelBufs b, const int32_t *gbase, uint32_t *flag) {
 // local id -> vertex, and each tail vertex's rewrite items (roff: the
 // triangle rows' offsets for h = 3, the adjacency's for h = 2)
 __global__ void k_te_glob(const uint32_t *flag, const uint32_t *loc, int32_t n, const int64_t *roff, int32_t *glob,
-                          int64_t *ib, int32_t *count) {
+                          int64_t *ib, int32_t A, int32_t *count) {
     for (int64_t v = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
         if (!flag[v]) continue;
         const uint32_t l = loc[v];
         glob[l] = (int32_t)v;
         ib[l] = (roff[v + 1] - roff[v] + TE_CH - 1) / TE_CH;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count = (int32_t)(loc[n - 1] + flag[n - 1]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *count = (int32_t)(loc[n - 1] + flag[n - 1]);
+        ib[A] = 0;
+    }
 }
 
 // The pairs of one rewrite item that stay inside the tail (a row holds every
@@ -2475,6 +2476,7 @@ __global__ void k_te_vsum(const int64_t *ib, const int64_t *kc, int32_t A, int64
         vcnt[l] = s;
         rl[l] = (s + 3) & ~(int64_t)3;
     }
+    if (blockIdx.x == 0 && threadIdx.x == 0) rl[A] = 0;
 }
 
 // where every rewrite item starts writing: its row's start plus the kept
@@ -2490,7 +2492,9 @@ __global__ void k_te_ioff(const int64_t *ib, const int64_t *lrow, int32_t A, int
     }
 }
 
-__global__ void k_te_pad(const int64_t *lrow, const int64_t *vcnt, int32_t A, uint32_t *lp) {
+// (and the engine's error flag cleared)
+__global__ void k_te_pad(const int64_t *lrow, const int64_t *vcnt, int32_t A, uint32_t *lp, int32_t *err) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *err = 0;
     for (int32_t l = blockIdx.x * blockDim.x + threadIdx.x; l < A; l += gridDim.x * blockDim.x)
         for (int64_t e = lrow[l] + vcnt[l]; e < lrow[l + 1]; e++) lp[e] = TE_NONE;
 }
@@ -3004,6 +3008,8 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
     }
 }
 
+__global__ void k_te_state(TeState *ts, TeState init) { *ts = init; }
+
 // item -> frontier position for a grid round (one wave per frontier vertex)
 __global__ void k_te_expand(const TeState *ts) {
     const uint32_t nF = ts->nF;
@@ -3217,9 +3223,7 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
     if (n_alive < 1) return -1;
     std::vector<GraphState> gst(b.G);
     int32_t round0 = 0;
-    DSD_HIP(hipMemcpyAsync(gst.data(), b.gs, (size_t)b.G * sizeof(GraphState), hipMemcpyDeviceToHost, s));
-    if (b.G > 1) DSD_HIP(hipMemcpyAsync(&round0, &b.ctl->round, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(gst.data(), b.gs, b.G).add(&round0, &b.ctl->round).run(s);
     std::vector<TeGraph> tg[3];                       // by workgroup: up to 2,048, 4,096 and TE_MAX vertices
     std::vector<int32_t> gbase(b.G, -1);
     int64_t total_a = 0, seen = 0;
@@ -3264,15 +3268,12 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
     }
     k_te_flags<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(b, dbase, flag);
     scan_exclusive_u32(flag, loc, n, s, sc);
-    fill_i32((int32_t *)(ib + A), 0, 2, s);
-    k_te_glob<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(flag, loc, n, roff, glob, ib, cnt);
+    k_te_glob<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(flag, loc, n, roff, glob, ib, A, cnt);
     scan_exclusive_i64(ib, ib, A + 1, s, sc);
-    int64_t hv[2] = {0, 0};
-    DSD_HIP(hipMemcpyAsync(&hv[0], ib + A, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(&hv[1], cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
-    const int64_t NI = hv[0];
-    if ((int32_t)hv[1] != A) throw Error(-3, "tail engine: the tail's vertex count disagrees with the alive count");
+    int64_t NI = 0;
+    int32_t tail_n = 0;
+    Readback(sc).add(&NI, ib + A).add(&tail_n, cnt).run(s);
+    if (tail_n != A) throw Error(-3, "tail engine: the tail's vertex count disagrees with the alive count");
     int64_t *kc = sc.get_n<int64_t>(NI + 1);
     const int gp = grid_for(NI, WAVES_PER_BLOCK, 8192), gA = grid_for(A, BLOCK, 1024);
     if (NI > 0) {
@@ -3281,12 +3282,10 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
     }
     // rows padded to four pairs, so that lanes load them four at a time
     int64_t *vcnt = sc.get_n<int64_t>(A), *lrow = sc.get_n<int64_t>(A + 1);
-    fill_i32((int32_t *)(lrow + A), 0, 2, s);
     k_te_vsum<<<gA, BLOCK, 0, s>>>(ib, kc, A, vcnt, lrow);
     scan_exclusive_i64(lrow, lrow, A + 1, s, sc);
     int64_t total = 0;
-    DSD_HIP(hipMemcpyAsync(&total, lrow + A, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&total, lrow + A).run(s);
     if (total > ppc * (int64_t)mu + 3 * (int64_t)A)
         throw Error(-3, "tail engine: more pairs than the tail's cliques allow");
     // (a graph's row starts are kept in 32 bits from its first row on)
@@ -3294,11 +3293,10 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         if (ppc * (int64_t)gst[x.g].mu_alive + 3 * (int64_t)x.A >= ((int64_t)1 << 32)) {
             if (b.G > 1 || total >= ((int64_t)1 << 32)) return -1;
         }
-    u64 walked = 0;   // pairs the engine walks: every kept pair once
+    u64 walked = 0, *d_walked = nullptr;   // pairs the engine walks: every kept pair once
     if (kt) {
-        u64 *s2 = sc.get_n<u64>(2);
-        sum_u64_128((const u64 *)kc, NI, s2, s, sc);
-        DSD_HIP(hipMemcpyAsync(&walked, s2, sizeof(u64), hipMemcpyDeviceToHost, s));
+        d_walked = sc.get_n<u64>(2);
+        sum_u64_128((const u64 *)kc, NI, d_walked, s, sc);
     }
     k_te_ioff<<<gA, BLOCK, 0, s>>>(ib, lrow, A, kc);
     uint32_t *lp = sc.get_n<uint32_t>(total);
@@ -3306,8 +3304,7 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         if (h == 3) k_te_pairs<true, 3><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp, b.gid, dbase);
         else k_te_pairs<true, 2><<<gp, BLOCK, 0, s>>>(roff, rdat, flag, loc, glob, ib, A, NI, kc, lp, b.gid, dbase);
     }
-    k_te_pad<<<gA, BLOCK, 0, s>>>(lrow, vcnt, A, lp);
-    fill_i32(cnt, 0, 1, s);
+    k_te_pad<<<gA, BLOCK, 0, s>>>(lrow, vcnt, A, lp, cnt);
     // the state for grid rounds (a single graph's; in a batch the other graphs keep the CUs busy)
     TeState *ts = nullptr;
     TeState hts{};
@@ -3318,7 +3315,7 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         hts.F = sc.get_n<uint32_t>(A);
         hts.ipre = sc.get_n<uint32_t>(A + 1);
         hts.imap = sc.get_n<uint32_t>(total / TE_ITEM + A + 1);   // items of one round: sum of ceil(row / TE_ITEM)
-        DSD_HIP(hipMemcpyAsync(ts, &hts, sizeof(TeState), hipMemcpyHostToDevice, s));
+        k_te_state<<<1, 1, 0, s>>>(ts, hts);
     }
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     if (kt && kt->time_main)
@@ -3345,9 +3342,12 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         if (ev[1]) DSD_HIP(hipEventRecord(ev[1], s));
         launches += 1;
         int32_t err = 0;
-        if (ts) DSD_HIP(hipMemcpyAsync(&hts, ts, sizeof(TeState), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(&err, cnt, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
+        Readback rb(sc);
+        rb.add(&err, cnt);
+        if (ts) rb.add(&hts, ts);
+        if (d_walked) rb.add(&walked, d_walked);
+        if (max_round) rb.add(max_round, &b.ctl->round);
+        rb.run(s);
         if (ev[0]) {
             float ms = 0;
             DSD_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
@@ -3377,10 +3377,6 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
     }
     for (auto &e : ev)
         if (e) (void)hipEventDestroy(e);
-    if (max_round) {
-        DSD_HIP(hipMemcpyAsync(max_round, &b.ctl->round, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
-    }
     const int64_t left = n_alive - total_a;
     k_te_close<<<1, BLOCK, 0, s>>>(b, (int32_t)left);
     if (kt) {
@@ -3524,10 +3520,8 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     k_init_graphs<<<grid_for(G, 256), 256, 0, s>>>(b, mu_dev, grp ? grp->lv_base : nullptr, k_floor);
     k_peel_init<<<grid_for(n, BLOCK, 4096), BLOCK, 0, s>>>(b, alive0, b.lists, &b.ctl->nlist[0]);
     k_start_graphs<<<grid_for(G, 256), 256, 0, s>>>(b);
-    int64_t *pinned = (int64_t *)thread_pinned();
-    DSD_HIP(hipMemcpyAsync(pinned, &b.ctl->n_alive, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
-    int64_t n_alive = pinned[0];
+    int64_t n_alive = 0;
+    Readback(sc).add(&n_alive, &b.ctl->n_alive).run(s);
     if (h >= 4 && !rootmode && n_alive > 0) {
         // the edges among the starting vertices, at most half the slots filled
         const int64_t pairs = n_alive * (n_alive - 1) / 2;
@@ -3671,9 +3665,7 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
         }
         if (tail) k_tail_finish<<<1, TAIL_BLOCK, 0, s>>>(b);
         steps += chunk;
-        DSD_HIP(hipMemcpyAsync(pinned, &b.ctl->n_alive, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
-        n_alive = pinned[0];
+        Readback(sc).add(&n_alive, &b.ctl->n_alive).run(s);
         if (steps > max_steps) throw Error(-3, "peel did not converge");
         if (chunk < 32) chunk *= 2;
     }
@@ -3699,9 +3691,18 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     }
     PeelCtl fin;
     std::vector<GraphState> gst(G);
-    DSD_HIP(hipMemcpyAsync(&fin, b.ctl, sizeof(PeelCtl), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(gst.data(), b.gs, G * sizeof(GraphState), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    // (a single graph's first levels come along)
+    const int64_t early = G == 1 ? std::min<int64_t>(lv_total, 512) : 0;
+    res.level_k.resize(early);
+    res.level_size.resize(early);
+    res.level_mu.resize(early);
+    Readback(sc)
+        .add(&fin, b.ctl)
+        .add(gst.data(), b.gs, G)
+        .add(res.level_k.data(), b.lv_k, early)
+        .add(res.level_size.data(), b.lv_size, early)
+        .add(res.level_mu.data(), b.lv_mu, early)
+        .run(s);
     if (fin.n_alive != 0) throw Error(-3, "peel ended with alive vertices");
     if (kt && b.count_work) {
         kt->main_pairs += fin.work[0];
@@ -3720,12 +3721,12 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     res.level_k.resize(ncopy);
     res.level_size.resize(ncopy);
     res.level_mu.resize(ncopy);
-    if (ncopy > 0) {
-        DSD_HIP(hipMemcpyAsync(res.level_k.data(), b.lv_k, ncopy * sizeof(u64), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(res.level_size.data(), b.lv_size, ncopy * sizeof(u64), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipMemcpyAsync(res.level_mu.data(), b.lv_mu, ncopy * sizeof(u64), hipMemcpyDeviceToHost, s));
-        DSD_HIP(hipStreamSynchronize(s));
-    }
+    if (ncopy > early)
+        Readback(sc)
+            .add(res.level_k.data() + early, b.lv_k + early, ncopy - early)
+            .add(res.level_size.data() + early, b.lv_size + early, ncopy - early)
+            .add(res.level_mu.data() + early, b.lv_mu + early, ncopy - early)
+            .run(s);
     if (G == 1 && gst[0].nlevels > 0) res.kmax = res.level_k.back();
     return res;
 }

@@ -28,6 +28,7 @@ public:
     template <typename T> T *get_n(int64_t n) { return (T *)get((size_t)(n > 0 ? n : 1) * sizeof(T)); }
     void reset() { cur_ = 0; off_ = 0; }
     size_t capacity() const;
+    bool external() const { return external_; }
 
 private:
     std::vector<std::pair<char *, size_t>> chunks_;
@@ -56,9 +57,30 @@ void sum_u64_128(const u64 *in, int64_t n, u64 *out2, hipStream_t s, Scratch &sc
 // free every recycled chunk of every device
 void release_chunk_pool();
 
-// a 64-byte pinned host buffer of the calling thread, for reading counters
-// back; allocated on first use and kept until the process ends
-void *thread_pinned();
+// Small values read back in one trip: a kernel gathers the pieces into a pinned
+// buffer of the calling thread, then one synchronisation.  (A copy into ordinary
+// host memory is a trip of its own, 10 to 12 us each.)  A piece too large for the
+// buffer, and every piece of a caller-owned scratch (sc), is copied as it is.
+class Readback {
+public:
+    explicit Readback(const Scratch &sc) : plain_(sc.external()) {}
+    // n values at dev, 4-byte aligned or single bytes
+    template <typename T> Readback &add(T *host, const T *dev, int64_t n = 1) {
+        piece(host, dev, (size_t)n * sizeof(T));
+        return *this;
+    }
+    // waits for the stream; the values are in place when it returns
+    void run(hipStream_t s);
+
+private:
+    static constexpr int PIECES = 8;
+    void piece(void *host, const void *dev, size_t bytes);
+    bool plain_;
+    int np_ = 0;
+    void *host_[PIECES];
+    const void *dev_[PIECES];
+    size_t bytes_[PIECES];
+};
 
 // fill helpers (kernels, usable under stream capture)
 void fill_u64(u64 *p, u64 v, int64_t n, hipStream_t s);

@@ -396,9 +396,7 @@ u64 tri_counts(const DevGraph &g, u64 *deg, TlCounts &w, hipStream_t s, Scratch 
     sum_u64_128(deg, n, sum, s, sc);
     u64 hs[2];
     int32_t err = 0;
-    DSD_HIP(hipMemcpyAsync(hs, sum, sizeof(hs), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(&err, b.err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(hs, sum, 2).add(&err, b.err).run(s);
     if (err) throw Error(-3, "triangle lists: a reverse arc is missing");
     if (hs[1] != 0 || hs[0] % 3 != 0) throw Error(-3, "triangle lists: clique-degree sum not a multiple of 3");
     w.mu = hs[0] / 3;
@@ -439,9 +437,7 @@ void build_tri_list(const DevGraph &g, TlCounts &w, TriList &tl, hipStream_t s, 
     k_tl_offsets_tail<<<1, 1, 0, s>>>(woff, w.cnt, arcs);
     int32_t err = 0;
     uint32_t total = 0;
-    DSD_HIP(hipMemcpyAsync(&err, b.err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipMemcpyAsync(&total, woff + arcs, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&err, b.err).add(&total, woff + arcs).run(s);
     if (err || (int64_t)total != tl.entries) {      // every reverse arc found, segments summing to 3 mu
         free_tri_list(tl);
         throw Error(-3, "triangle lists do not match their counts");
@@ -453,8 +449,7 @@ void build_tri_list(const DevGraph &g, TlCounts &w, TriList &tl, hipStream_t s, 
     k_tl_mid<<<4096, BLOCK, 0, s>>>(b);
     k_tl_big<<<1024, BLOCK, 0, s>>>(b);
     k_tl_check<<<grid_for(arcs, BLOCK, 4096), BLOCK, 0, s>>>(b.cnt, woff, arcs, b.err);
-    DSD_HIP(hipMemcpyAsync(&err, b.err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    DSD_HIP(hipStreamSynchronize(s));
+    Readback(sc).add(&err, b.err).run(s);
     if (err) {
         free_tri_list(tl);
         throw Error(-3, "triangle lists do not match their counts");
