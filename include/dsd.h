@@ -58,7 +58,7 @@ typedef struct dsd_graph_s *dsd_graph;
 typedef struct { uint64_t num, den; } dsd_rational;
 
 /* Per-call timing and size statistics (all times in milliseconds, measured
- * with HIP events on the graph's stream).  Filled by every compute call when
+ * on the graph's stream: stages on the host's clock, kernels with HIP events).  Filled by every compute call when
  * the caller passes a non-NULL pointer to dsd_last_stats. */
 typedef struct {
     double t_orient_ms, t_enum_ms, t_peel_ms, t_locate_ms, t_exact_ms, t_total_ms;
