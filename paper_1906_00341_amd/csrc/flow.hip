@@ -89,6 +89,29 @@ __global__ void k_csr_count(const int *eu, const int *ev, int64_t E, uint32_t *c
 // workgroup; every workgroup walks one contiguous range of arcs.
 constexpr int CSR_HOT = 8192;
 
+// (Arc counts and the fill of a network of 4.3 million arcs: 4.6 -> 2.8 ms.)
+// The cold nodes (of edges) come in runs: a triangle's three arcs name three of
+// them, and one of the three stays the same over the triangles of an edge.  So the
+// lanes that name what one of the first three lanes names add with one atomic.
+// Returns the lane's place in its node's row (all lanes of the wave call this).
+__device__ __forceinline__ uint32_t csr_cold(uint32_t *cnt, int v, bool cold) {
+    uint32_t pos = 0;
+    u64 left = __ballot(cold);
+#pragma unroll
+    for (int l = 0; l < 3; l++) {
+        const u64 m = __ballot(cold && v == __shfl(v, l, WAVE)) & left;
+        if (__popcll(m) < 2) continue;
+        const int first = __builtin_ctzll(m);
+        uint32_t base = 0;
+        if (lane() == first) base = atomicAdd(&cnt[v], (uint32_t)__popcll(m));
+        base = __shfl(base, first, WAVE);
+        if (m >> lane() & 1) pos = base + (uint32_t)__popcll(m & lanemask_lt());
+        left &= ~m;
+    }
+    if (left >> lane() & 1) pos = atomicAdd(&cnt[v], 1u);
+    return pos;
+}
+
 __device__ __forceinline__ void csr_range(int64_t E, int64_t *lo, int64_t *hi) {
     const int64_t per = (E + gridDim.x - 1) / gridDim.x;
     *lo = min(E, (int64_t)blockIdx.x * per);
@@ -102,12 +125,13 @@ __global__ __launch_bounds__(BLOCK) void k_csr_count_hot(const int *eu, const in
     __syncthreads();
     int64_t lo, hi;
     csr_range(E, &lo, &hi);
-    for (int64_t i = lo + threadIdx.x; i < hi; i += BLOCK) {
-        const int u = eu[i], v = ev[i];
-        if (u < hot) atomicAdd(&sc[u], 1u);
-        else atomicAdd(&cnt[u], 1u);
-        if (v < hot) atomicAdd(&sc[v], 1u);
-        else atomicAdd(&cnt[v], 1u);
+    for (int64_t i0 = lo; i0 < hi; i0 += BLOCK) {
+        const int64_t i = i0 + threadIdx.x;
+        const int u = i < hi ? eu[i] : 0, v = i < hi ? ev[i] : 0;
+        if (i < hi && u < hot) atomicAdd(&sc[u], 1u);
+        if (i < hi && v < hot) atomicAdd(&sc[v], 1u);
+        csr_cold(cnt, u, i < hi && u >= hot);
+        csr_cold(cnt, v, i < hi && v >= hot);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < hot; i += BLOCK)
@@ -131,10 +155,14 @@ __global__ __launch_bounds__(BLOCK) void k_csr_fill_hot(const int *eu, const int
     for (int i = threadIdx.x; i < hot; i += BLOCK)
         if (sc[i]) sc[i] = atomicAdd(&fill[i], sc[i]);
     __syncthreads();
-    for (int64_t i = lo + threadIdx.x; i < hi; i += BLOCK) {
-        const int u = eu[i], v = ev[i];
-        const int pu = (int)(u < hot ? atomicAdd(&sc[u], 1u) : atomicAdd(&fill[u], 1u));
-        const int pv = (int)(v < hot ? atomicAdd(&sc[v], 1u) : atomicAdd(&fill[v], 1u));
+    for (int64_t i0 = lo; i0 < hi; i0 += BLOCK) {
+        const int64_t i = i0 + threadIdx.x;
+        const bool in = i < hi;
+        const int u = in ? eu[i] : 0, v = in ? ev[i] : 0;
+        int pu = (int)csr_cold(fill, u, in && u >= hot), pv = (int)csr_cold(fill, v, in && v >= hot);
+        if (!in) continue;
+        if (u < hot) pu = (int)atomicAdd(&sc[u], 1u);
+        if (v < hot) pv = (int)atomicAdd(&sc[v], 1u);
         to[pu] = v;
         to[pv] = u;
         rev[pu] = pv;
@@ -354,13 +382,83 @@ __device__ __forceinline__ void bfs_push(const FlowBufs &b, bool take, int u, in
     if (big) b.bfront[nx][base_b + __popcll(mb & lanemask_lt())] = u;
 }
 
+// A level with a wide frontier is taken from the other side: every unlabelled
+// node looks for an arc into the frontier among its own, in order, and stops at
+// the first.  Pushed from the frontier, such a level is bound by atomics: a
+// node's label is claimed again by every XCD that has not seen it yet (the 240
+// vertex nodes of a triangle network by 4 million arcs: 0.6 ms), and every wave
+// that labels adds to one counter (0.9 ms for its edge nodes).  Pulled, they take
+// 0.05 to 0.15 ms: the searches of one exact step 12 -> 2.8 ms.  A node is in the
+// frontier once, so at most 16 levels of a search are wide on either count.
+__device__ __forceinline__ bool bfs_wide(const FlowBufs &b, int cur) {
+    const int nf = b.nfront[cur], nb = b.nbfront[cur];
+    return nf >= max(256, b.n / 16) || (nb >= 4 && (int64_t)16 * nb >= b.nbig);
+}
+
+// labelled nodes gathered in LDS, then added to a frontier list with one atomic
+template <int CAP>
+struct BfsQueue {
+    int v[CAP];
+    int n, base;
+};
+// all threads of the block call this together
+template <int CAP, int THREADS>
+__device__ __forceinline__ void bfs_flush(BfsQueue<CAP> &q, int *list, int *count) {
+    __syncthreads();
+    if (threadIdx.x == 0 && q.n) q.base = atomicAdd(count, q.n);
+    __syncthreads();
+    for (int i = threadIdx.x; i < q.n; i += THREADS) list[q.base + i] = q.v[i];
+    __syncthreads();
+    if (threadIdx.x == 0) q.n = 0;
+    __syncthreads();
+}
+
 // one level: every node of front[cur] (height `level`; the frontier nodes
 // with at most BIG_ARCS arcs) labels its unlabelled
-// in-neighbours (u with a residual arc u -> v) level + 1
+// in-neighbours (u with a residual arc u -> v) level + 1; in a wide level
+// (bfs_wide) every unlabelled node of at most BIG_ARCS arcs looks for one itself
+constexpr int PULL_BLOCKS = 2048, PULL_QUEUE = 1024;
 __global__ __launch_bounds__(BLOCK) void k_bfs_level(FlowBufs b, int cur, int level) {
+    const int wv = threadIdx.x / WAVE;
+    if (bfs_wide(b, cur)) {
+        __shared__ BfsQueue<PULL_QUEUE> q;
+        if (threadIdx.x == 0) q.n = 0;
+        __syncthreads();
+        if (blockIdx.x >= PULL_BLOCKS) return;
+        const int nb = min((int)gridDim.x, PULL_BLOCKS);
+        // a wave labels at most one node a step: the block's four fit while PULL_QUEUE - 4 are waiting
+        for (int u0 = blockIdx.x * WAVES_PER_BLOCK; u0 < b.n; u0 += nb * WAVES_PER_BLOCK) {
+            const int u = u0 + wv;
+            const int a0 = u < b.n ? b.first[u] : 0, a1 = u < b.n ? b.first[u + 1] : 0;
+            if (u < b.n && u != b.s && a1 - a0 <= BIG_ARCS && b.ht[u] == b.n) {
+                bool found = false;
+                for (int a = a0 + lane(); a - lane() < a1 && !found; a += 4 * WAVE) {
+                    int64_t c[4];
+                    int v[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        const int at = min(a + k * WAVE, a1 - 1);   // (a lane past the end looks at the last arc)
+                        c[k] = b.cf[at];
+                        v[k] = b.to[at];
+                    }
+                    bool hit = false;
+#pragma unroll
+                    for (int k = 0; k < 4; k++) hit |= (c[k] > 0) & (b.ht[v[k]] == level);
+                    found = __ballot(hit) != 0;
+                }
+                if (found && lane() == 0) {
+                    b.ht[u] = level + 1;
+                    q.v[atomicAdd(&q.n, 1)] = u;
+                }
+            }
+            if (__syncthreads_or(q.n > PULL_QUEUE - 2 * WAVES_PER_BLOCK))
+                bfs_flush<PULL_QUEUE, BLOCK>(q, b.front[cur ^ 1], &b.nfront[cur ^ 1]);
+        }
+        bfs_flush<PULL_QUEUE, BLOCK>(q, b.front[cur ^ 1], &b.nfront[cur ^ 1]);
+        return;
+    }
     const int nf = b.nfront[cur];
     const int *F = b.front[cur];
-    const int wv = threadIdx.x / WAVE;
     for (int i = blockIdx.x * WAVES_PER_BLOCK + wv; i < nf; i += gridDim.x * WAVES_PER_BLOCK) {
         const int v = F[i];
         for (int a0 = b.first[v]; a0 < b.first[v + 1]; a0 += WAVE) {
@@ -378,11 +476,36 @@ __global__ __launch_bounds__(BLOCK) void k_bfs_level(FlowBufs b, int cur, int le
     }
 }
 
-// the same for frontier nodes with more than BIG_ARCS arcs: one block each
+// the same for frontier nodes (wide level: unlabelled nodes) with more than BIG_ARCS arcs: one block each
 __global__ __launch_bounds__(BIG_BLOCK) void k_bfs_level_big(FlowBufs b, int cur, int level) {
+    constexpr int K = 4;   // arcs per thread per step: their loads go out together
+    if (bfs_wide(b, cur)) {
+        for (int i = blockIdx.x; i < b.nbig; i += gridDim.x) {
+            const int u = b.big[i];
+            if (u == b.s || b.ht[u] != b.n) continue;   // (only this block labels u: the same for every thread)
+            const int end = b.first[u + 1];
+            bool found = false;
+            for (int a0 = b.first[u]; a0 < end && !found; a0 += BIG_BLOCK * K) {
+                bool hit = false;
+#pragma unroll
+                for (int k = 0; k < K; k++) {
+                    const int a = min(a0 + k * BIG_BLOCK + (int)threadIdx.x, end - 1);
+                    hit |= (b.cf[a] > 0) & (b.ht[b.to[a]] == level);
+                }
+                found = __syncthreads_or(hit);
+            }
+            if (found && threadIdx.x == 0) {
+                b.ht[u] = level + 1;
+                b.bfront[cur ^ 1][atomicAdd(&b.nbfront[cur ^ 1], 1)] = u;
+            }
+        }
+        return;
+    }
     const int nf = b.nbfront[cur];
     const int *F = b.bfront[cur];
-    constexpr int K = 4;   // arcs per thread per step: their loads go out together
+    __shared__ BfsQueue<2 * BIG_BLOCK * K> q;   // nodes of at most BIG_ARCS arcs
+    if (threadIdx.x == 0) q.n = 0;
+    __syncthreads();
     for (int i = blockIdx.x; i < nf; i += gridDim.x) {
         const int v = F[i];
         const int end = b.first[v + 1];
@@ -401,11 +524,17 @@ __global__ __launch_bounds__(BIG_BLOCK) void k_bfs_level_big(FlowBufs b, int cur
             }
 #pragma unroll
             for (int k = 0; k < K; k++) {
-                const bool take = cand[k] && atomicCAS(&b.ht[u[k]], b.n, level + 1) == b.n;
-                if (__ballot(take)) bfs_push(b, take, u[k], cur ^ 1);
+                if (!cand[k] || atomicCAS(&b.ht[u[k]], b.n, level + 1) != b.n) continue;
+                if (b.first[u[k] + 1] - b.first[u[k]] > BIG_ARCS)
+                    b.bfront[cur ^ 1][atomicAdd(&b.nbfront[cur ^ 1], 1)] = u[k];
+                else
+                    q.v[atomicAdd(&q.n, 1)] = u[k];
             }
+            if (__syncthreads_or(q.n > BIG_BLOCK * K))   // (the next step adds at most BIG_BLOCK * K)
+                bfs_flush<2 * BIG_BLOCK * K, BIG_BLOCK>(q, b.front[cur ^ 1], &b.nfront[cur ^ 1]);
         }
     }
+    bfs_flush<2 * BIG_BLOCK * K, BIG_BLOCK>(q, b.front[cur ^ 1], &b.nfront[cur ^ 1]);
 }
 
 __global__ void k_bfs_reset(FlowBufs b, int cur) {
