@@ -537,6 +537,11 @@ std::vector<TuneResult> autotune(const DevGraph &g, int h, hipStream_t s, Scratc
                 tr.cap_best = cap;
             }
         }
+        // (a smaller grid within 2 % of the built-in one, but behind it, gives way)
+        if (tr.ms_default < best) {
+            best = tr.ms_default;
+            tr.cap_best = def;
+        }
         tr.ms_best = best;
         out.push_back(tr);
         TuneTable &t = tune_table();
