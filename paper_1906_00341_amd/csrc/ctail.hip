@@ -51,7 +51,7 @@ constexpr u64 CT_TASK_MASK = (1ull << CT_ITEM_SHIFT) - 1ull;
 // rows of AW words (a cycle each) and d^2 member pairs (a quarter of a cycle
 // each; R > 3: d^3 / 64 for the counting).  The grid's three launches and the
 // engine's restart cost about as much (40 us).
-constexpr u64 CT_LIGHT = 100000;
+constexpr u64 CT_LIGHT = (u64)CT_ROUND;
 constexpr int CT_FRONT = 32;
 // Two waves per SIMD: what every wave does alike (the level, the frontier,
 // the control between barriers) is issued by each of them, so sixteen waves

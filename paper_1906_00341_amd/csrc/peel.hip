@@ -2383,7 +2383,8 @@ __global__ void k_last_row(int64_t *nrow, const int64_t *cnt, int32_t n) {
 }
 
 // Rebuild b.row_ptr / b.col / b.dag_off over the vertices still taking part.
-static void compact_adjacency(PeelBufs &b, hipStream_t s, Scratch &sc) {
+// (returns the entries left)
+static int64_t compact_adjacency(PeelBufs &b, hipStream_t s, Scratch &sc) {
     const int32_t n = b.n;
     int64_t *cnt = sc.get_n<int64_t>(n);
     int32_t *cnt_out = sc.get_n<int32_t>(n);
@@ -2406,6 +2407,7 @@ static void compact_adjacency(PeelBufs &b, hipStream_t s, Scratch &sc) {
         k_reset_chunks<<<1, 1, 0, s>>>(b);
         k_rechunk<<<256, BLOCK, 0, s>>>(b);
     }
+    return total;
 }
 
 // ---------------------------------------------------------------- host driver
@@ -3700,16 +3702,28 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     int64_t steps = 0, chunk = 4;
     const int64_t max_steps = 4 * (int64_t)n + 64;
     const bool compacting = !listed;
-    int64_t compacted_at = n;
+    int64_t compacted_at = n, entries = 2 * g.m;
     // h >= 4: the clique tail takes over once it can.  A graph that starts
     // small (CoreApp's G[W]) goes at once; else the first rounds, which take
     // the many vertices in few cliques, come first: the matrix of what they
     // leave is many times smaller.
     const bool ctail = rootmode && h >= 4;
     constexpr int64_t CT_AT_ONCE = 16384;
+    // Above that many vertices the tail pays only while its one workgroup can
+    // keep a typical round: by the clique tail's own cost of a vertex of the
+    // average degree (as many matrix rows of n_alive / 64 words, a quarter of a
+    // cycle per pair of members).  Otherwise every round goes to the grid and
+    // back: R-MAT scale 22, h = 4, whose alive vertices keep some hundreds of
+    // neighbours each, hands over 64,207 of its 66,404 rounds at 80 us each
+    // (peel 6.0 s without this rule, 4.4 s with it; 4.9 s when the rule also
+    // keeps the last 16,384 vertices out).
+    auto ct_light = [&](int64_t alive, int64_t at, int64_t adj) {
+        const int64_t d = at > 0 ? adj / at : 0;
+        return alive <= CT_AT_ONCE || d * (alive / WAVE) + d * d / 4 <= CT_ROUND;
+    };
     if (ctail && G == 1 && n_alive > 0 && n_alive <= CT_AT_ONCE && clique_tail(b, h, n_alive, s, sc, kt)) n_alive = 0;
     if (compacting && n_alive > 0 && n_alive < n / 2) {
-        compact_adjacency(b, s, sc);
+        entries = compact_adjacency(b, s, sc);
         compacted_at = n_alive;
     }
     const bool engine = (listed || h == 2) && pattern == 0;
@@ -3728,12 +3742,16 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
         if (engine && (G == 1 ? n_alive <= TE_MAX : steps > 0 && n_alive < (int64_t)G * TE_MAX) &&
             tail_engine(b, h, n_alive, false, s, sc, kt, nullptr) == 0)
             break;
-        if (ctail && steps > 0 && clique_tail(b, h, n_alive, s, sc, kt)) break;
+        if (ctail && steps > 0 && G > 1 && clique_tail(b, h, n_alive, s, sc, kt)) break;
         if (compacting && n_alive < compacted_at / 2) {
-            compact_adjacency(b, s, sc);
+            entries = compact_adjacency(b, s, sc);
             compacted_at = n_alive;
             graphs.reset();
         }
+        // (after the compaction: entries is then of at most twice as many vertices)
+        if (ctail && steps > 0 && G == 1 && ct_light(n_alive, compacted_at, entries) &&
+            clique_tail(b, h, n_alive, s, sc, kt))
+            break;
         if (n_alive <= TAIL_ALIVE) tail = true;
         const int gp = tail ? gtail : gprobe, gq = tail ? gtail : gproc, gf = tail ? gtail : gbuild;
         // one round's kernels; they read the round's state from the device,

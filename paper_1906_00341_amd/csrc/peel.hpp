@@ -95,7 +95,9 @@ struct PeelBufs {
 // Finishes the peel of b's graphs (between two rounds) once their alive
 // vertices are few enough for adjacency bitmaps; min_degree as in peel().
 // Returns false, having changed nothing, when they are not (or with
-// DSD_TAIL_ENGINE=0).
+// DSD_TAIL_ENGINE=0).  CT_ROUND: cycles up to which its workgroup keeps a
+// round to itself.
+constexpr int64_t CT_ROUND = 100000;
 bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scratch &sc, KernelTimes *kt);
 
 }  // namespace dsd
