@@ -1688,6 +1688,20 @@ struct RootLds {
 template <int RR, int W>
 __device__ u64 root_member_work(int x, const u64 *S, const u64 *mask, u64 *cnt, u64 *sA, u64 *sB, int32_t *q) {
     const int L = lane();
+    if constexpr (RR == 2) {
+        // An edge has no middle: y counts it as its own last member.  (By itself,
+        // so that the h = 4 kernel inlines this: called, it keeps 400 bytes a lane
+        // in scratch, and each launch, most of them empty, takes 5 us longer.)
+        u64 above = 0, below = 0;
+        for (int w = L; w < W; w += WAVE) {
+            above += (u64)__popcll(row_above<W>(S, x, w) & mask[w]);
+            below += (u64)__popcll(row_below<W>(S, x, w) & mask[w]);
+        }
+        above = wave_sum(above);
+        below = wave_sum(below);
+        if (L == 0 && above + below) atomicAdd(&cnt[x], above + below);
+        return above;
+    }
     for (int w = L; w < W; w += WAVE) {
         sA[w] = row_above<W>(S, x, w) & mask[w];
         sB[w] = row_below<W>(S, x, w) & mask[w];
@@ -1702,11 +1716,7 @@ __device__ u64 root_member_work(int x, const u64 *S, const u64 *mask, u64 *cnt, 
         auto drain = [&](int take) {
             if (L < take) {
                 const int y = q[L];
-                if constexpr (RR == 2) {
-                    // an edge has no middle: y counts it as its own last member
-                    if (role == 0) first += 1;
-                    else last += 1;
-                } else if constexpr (RR == 3) {
+                if constexpr (RR == 3) {
                     // popcounts streamed over the words at and above y's
                     u64 cy = 0;
 #pragma unroll 4
@@ -1719,7 +1729,7 @@ __device__ u64 root_member_work(int x, const u64 *S, const u64 *mask, u64 *cnt, 
                     } else {
                         last += cy;
                     }
-                } else {
+                } else if constexpr (RR >= 4) {
                     u64 M2[W];
 #pragma unroll
                     for (int k = 0; k < W; k++) M2[k] = X[k] & row_above<W>(S, y, k);
