@@ -3719,17 +3719,27 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     // leave is many times smaller.
     const bool ctail = rootmode && h >= 4;
     constexpr int64_t CT_AT_ONCE = 16384;
-    // Above that many vertices the tail pays only while its one workgroup can
+    // From this many vertices on the tail takes every peel that is in its
+    // rounds.  h = 4: R-MAT scale 22 (average degree 1,071 there, so that every
+    // round is handed over) 3.86 s of peel against 4.12 s with the round
+    // kernels to the end, scale 20 (degree 544) 1.32 against 1.56.  h >= 5: the
+    // grid counts a wide set more slowly than the round kernels do, by more than
+    // the launches it saves: h = 5 on scale 22 35.6 s from 16,384 vertices on,
+    // 32.2 from 8,192, 30.5 from 4,096, 29.9 from 2,048 and 30.8 without the
+    // tail; on scale 21 23.1, 22.8, 18.7, 18.2 and 18.3.
+    const int64_t ct_always = h == 4 ? CT_AT_ONCE : 2048;
+    // Above that the tail pays only while its one workgroup can
     // keep a typical round: by the clique tail's own cost of a vertex of the
     // average degree (as many matrix rows of n_alive / 64 words, a quarter of a
     // cycle per pair of members).  Otherwise every round goes to the grid and
     // back: R-MAT scale 22, h = 4, whose alive vertices keep some hundreds of
     // neighbours each, hands over 64,207 of its 66,404 rounds at 80 us each
-    // (peel 6.0 s without this rule, 4.4 s with it; 4.9 s when the rule also
-    // keeps the last 16,384 vertices out).
+    // (peel 6.0 s without this rule, 4.4 s with it).  The counting (h >= 5:
+    // d^3 / 64 more) is left out: R-MAT scale 18, h = 5 enters later with it
+    // (29,340 vertices alive instead of 42,530), 0.96 s of peel instead of 0.92.
     auto ct_light = [&](int64_t alive, int64_t at, int64_t adj) {
         const int64_t d = at > 0 ? adj / at : 0;
-        return alive <= CT_AT_ONCE || d * (alive / WAVE) + d * d / 4 <= CT_ROUND;
+        return alive <= ct_always || d * (alive / WAVE) + d * d / 4 <= CT_ROUND;
     };
     if (ctail && G == 1 && n_alive > 0 && n_alive <= CT_AT_ONCE && clique_tail(b, h, n_alive, s, sc, kt)) n_alive = 0;
     if (compacting && n_alive > 0 && n_alive < n / 2) {
