@@ -49,8 +49,13 @@ constexpr u64 CT_TASK_MASK = (1ull << CT_ITEM_SHIFT) - 1ull;
 // One workgroup keeps a round of at most CT_FRONT frontier vertices whose
 // cost it puts at no more than CT_LIGHT: per vertex of d members, d matrix
 // rows of AW words (a cycle each) and d^2 member pairs (a quarter of a cycle
-// each; R > 3: d^3 / 64 for the counting).  The grid's three launches and the
-// engine's restart cost about as much (40 us).
+// each; R > 3: d^3 / 64 for the counting; R = 5: d^4 / 64, as every triangle
+// walks its common neighbours).  The grid's three launches and the engine's
+// restart cost about as much (40 us).  h = 6 without the last term: rounds of
+// milliseconds on one workgroup, core peel of R-MAT scale 16 / 17 2.67 / 9.84 s
+// instead of 0.88 / 3.98 (CoreApp of scale 14 0.51 s instead of 0.15; none of
+// the tail: 3.97 / 8.26 and 0.29); d^4 / 128 and / 256 measure 0.87 and 0.90 s
+// at scale 16, 0.091 and 0.111 at scale 13 (d^4 / 64: 0.085).
 constexpr u64 CT_LIGHT = (u64)CT_ROUND;
 constexpr int CT_FRONT = 32;
 // Two waves per SIMD: what every wave does alike (the level, the frontier,
@@ -1107,7 +1112,7 @@ __global__ __launch_bounds__(CT_BLOCK) void k_ct_engine(PeelBufs b, CtBufs q, co
                     const int st = ct_lds_stride(ct_lds_words(d));
                     if (L == 0) {
                         const u64 dd = (u64)d * (u64)d;
-                        const u64 pairs = (u64)d * (u64)AW + dd / 4 + (R > 3 ? dd * (u64)d / 64 : 0);
+                        const u64 pairs = (u64)d * (u64)AW + dd / 4 + (R > 3 ? dd * (u64)d / 64 : 0) + (R > 4 ? dd * dd / 64 : 0);
                         if (d > DC || atomicAdd(&sPairs[p], pairs) + pairs > CT_LIGHT) {
                             q.hlist[hsel][base + atomicAdd(&sNH[p], 1)] = v;
                             vi = -2;                 // the grid takes it

@@ -5,7 +5,7 @@ from math import comb
 import numpy as np
 import pytest
 
-from paper_1906_00341_amd import dsd
+from paper_1906_00341_amd import dsd, synth
 from test_gpu_clique_tail import _cliques
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +25,22 @@ def test_dense_vertices_stay_with_the_round_kernels():
     want = np.concatenate([np.full(m, comb(m - 1, 4), np.uint64) for m in sizes])
     np.testing.assert_array_equal(np.sort(core), np.sort(want))
     assert 0 < st["k4_tail_vertices"] < 14000
+
+
+def test_six_clique_rounds_go_to_the_grid(monkeypatch):
+    # single vertices of 50 to 150 members leave round after round: their
+    # 5-cliques are a walk over the common neighbours of every triangle, more
+    # than the workgroup keeps
+    n, s, d = synth.rmat(scale=13, edge_factor=16, seed=5)
+    got = {}
+    for engine in ("1", "0"):
+        monkeypatch.setenv("DSD_TAIL_ENGINE", engine)
+        g = dsd.build_csr(n, s, d)
+        core, km = dsd.clique_core(g, 6)
+        got[engine] = core, km, g.stats()
+        g.free()
+    np.testing.assert_array_equal(got["1"][0], got["0"][0])
+    assert got["1"][1] == got["0"][1]
+    st = got["1"][2]
+    assert st["k4_tail_launches"] > 0
+    assert st["k4_tail_grid_pairs"] > st["k4_tail_pairs"]
