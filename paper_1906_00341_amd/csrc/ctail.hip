@@ -1466,7 +1466,11 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
     const char *env = std::getenv("DSD_TAIL_ENGINE");
     if (env && std::strcmp(env, "0") == 0) return false;
     const int R = h - 1;
-    bool first = true;
+    // allocated for the first matrix; those built again for fewer vertices fit
+    // in the same buffers (a peel that is under way asks for no more memory)
+    CtBufs q{};
+    uint32_t *flag = nullptr, *loc = nullptr;
+    int32_t *lists = nullptr;
     while (true) {
         if (n_alive < 1 || n_alive > CT_VERTICES || (b.G == 1 && n_alive > CT_MAX)) return false;
         std::vector<GraphState> gs(b.G);
@@ -1507,34 +1511,40 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
         }
         // a removed vertex's members with their compact rows, at worst all of its graph
         const int64_t one = widest / 2 + 1 + widest * std::max<int64_t>(8, (widest + 63) / 64);
-        const int64_t acap = std::max<int64_t>(one, std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
-        if (first) {
+        if (!q.ctl) {
+            const int64_t acap = std::max<int64_t>(one, std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
             size_t free_b = 0, total_b = 0;
             const size_t need = 8 * (size_t)(words + acap + 2 * sets) + 112 * (size_t)total;
             if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4) return false;
+            q.R = R;
+            q.minpeel = b.minpeel;
+            q.acap = acap;
+            try {
+                q.cg = sc.get_n<CtGraph>((int64_t)cg.size());
+                q.glob = sc.get_n<int32_t>(total);
+                q.ldeg = sc.get_n<u64>(total);
+                q.M = sc.get_n<u64>(words);
+                q.lb = sc.get_n<u64>(sets);
+                q.cb = sc.get_n<u64>(sets);
+                q.hlist[0] = sc.get_n<int32_t>(total);
+                q.hlist[1] = sc.get_n<int32_t>(total);
+                q.items[0] = sc.get_n<CtItem>(total);
+                q.items[1] = sc.get_n<CtItem>(total);
+                q.cand = sc.get_n<int32_t>(total);
+                q.front[0] = sc.get_n<CtFront>(total);
+                q.front[1] = sc.get_n<CtFront>(total);
+                q.arena = sc.get_n<u64>(acap);
+                flag = sc.get_n<uint32_t>(b.n);
+                loc = sc.get_n<uint32_t>(b.n);
+                lists = sc.get_n<int32_t>((int64_t)cg.size());
+                q.ctl = sc.get_n<CtCtl>(1);
+            } catch (const Error &e) {
+                // another stream's work took the memory meanwhile: the round kernels go on
+                if (e.status != -2 || sc.external()) throw;
+                (void)hipGetLastError();
+                return false;
+            }
         }
-        first = false;
-        CtBufs q{};
-        q.R = R;
-        q.minpeel = b.minpeel;
-        q.acap = acap;
-        q.ctl = sc.get_n<CtCtl>(1);
-        q.cg = sc.get_n<CtGraph>((int64_t)cg.size());
-        q.glob = sc.get_n<int32_t>(total);
-        q.ldeg = sc.get_n<u64>(total);
-        q.M = sc.get_n<u64>(words);
-        q.lb = sc.get_n<u64>(sets);
-        q.cb = sc.get_n<u64>(sets);
-        q.hlist[0] = sc.get_n<int32_t>(total);
-        q.hlist[1] = sc.get_n<int32_t>(total);
-        q.items[0] = sc.get_n<CtItem>(total);
-        q.items[1] = sc.get_n<CtItem>(total);
-        q.cand = sc.get_n<int32_t>(total);
-        q.front[0] = sc.get_n<CtFront>(total);
-        q.front[1] = sc.get_n<CtFront>(total);
-        q.arena = sc.get_n<u64>(acap);
-        uint32_t *flag = sc.get_n<uint32_t>(b.n), *loc = sc.get_n<uint32_t>(b.n);
-        int32_t *lists = sc.get_n<int32_t>((int64_t)cg.size());
         small.insert(small.end(), large.begin(), large.end());     // both lists in one upload
         const int nlarge = (int)large.size(), nsmall = (int)small.size() - nlarge;
         fill_i32((int32_t *)q.ctl, 0, (int64_t)(sizeof(CtCtl) / sizeof(int32_t)), s);

@@ -44,3 +44,25 @@ def test_six_clique_rounds_go_to_the_grid(monkeypatch):
     st = got["1"][2]
     assert st["k4_tail_launches"] > 0
     assert st["k4_tail_grid_pairs"] > st["k4_tail_pairs"]
+
+
+def test_matrix_rebuilds_take_no_more_memory(monkeypatch):
+    # 60,060 vertices in cliques of 5 to 60: the matrix is rebuilt four times on the way
+    torch = pytest.importorskip("torch")
+    dsd.load()
+    n, s, d = _cliques(list(range(5, 61)) * 33)
+    used = {}
+    for engine in ("0", "1"):
+        monkeypatch.setenv("DSD_TAIL_ENGINE", engine)
+        dsd.release_cache()
+        before = torch.cuda.mem_get_info()[0]
+        g = dsd.build_csr(n, s, d)
+        _, km = dsd.clique_core(g, 4)
+        st = g.stats()
+        g.free()                                     # (its memory stays for the next handle)
+        used[engine] = before - torch.cuda.mem_get_info()[0]
+        assert km == comb(59, 3)
+    assert st["k4_tail_vertices"] > n                # rebuilt: some vertices count again
+    words = n * -(-n // 64)
+    need = 8 * 2 * words + 256 * n                   # the first matrix, one vertex's worst case beside it, lists
+    assert used["1"] - used["0"] < need + (256 << 20)   # (memory comes in chunks of 64 MiB and more)
