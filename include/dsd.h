@@ -405,7 +405,10 @@ dsd_status dsd_batch_run(int32_t count, const dsd_graph *graphs, const int *h, i
  * small requests never wait behind large ones alone.  A request's footprint
  * is estimated as 160 bytes per vertex plus 192 bytes per edge (the peel's
  * buffers dominate); one that could never fit hbm_budget_bytes is refused at
- * submit with DSD_ENOMEM.  At most max_slots requests are queued or running
+ * submit with DSD_ENOMEM.  The adjacency bitmaps of an h >= 4 peel (a bit per
+ * pair of the vertices still in it, and about as much again) come out of what
+ * is left of the budget when the peel wants them; where they do not fit, the
+ * peel goes on without them.  At most max_slots requests are queued or running
  * at once (DSD_EBUSY beyond).  A queued request may be overtaken by later
  * ones that fit while it does not. */
 typedef struct dsd_server_s *dsd_server;

@@ -127,6 +127,7 @@ void run_group(const std::vector<int32_t> &idx, int h, int op, const dsd_graph *
     hipStream_t s = G0->stream;
     for (int32_t i : idx) DSD_HIP(hipStreamSynchronize(graphs[i]->stream));
     Scratch sc;
+    sc.set_grant(G0->sc.grant());
     std::vector<UnionDesc> desc(G);
     std::vector<int64_t> voff(G), eoff(G), lvb(G);
     int64_t N = 0, E = 0;

@@ -1515,7 +1515,8 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
             const int64_t acap = std::max<int64_t>(one, std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
             size_t free_b = 0, total_b = 0;
             const size_t need = 8 * (size_t)(words + acap + 2 * sets) + 112 * (size_t)total;
-            if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4) return false;
+            if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 || !sc.may_take(need))
+                return false;
             q.R = R;
             q.minpeel = b.minpeel;
             q.acap = acap;

@@ -7,6 +7,17 @@
 
 namespace dsd {
 
+// Device memory beyond what a call was admitted with (a server's budget).
+// take: bytes, or nothing and false where they do not fit; safe with several
+// threads.  What was taken goes back with the call's end.
+class MemoryGrant {
+public:
+    virtual bool take(size_t bytes) = 0;
+
+protected:
+    ~MemoryGrant() = default;
+};
+
 // Bump allocator over device chunks; reset() recycles everything (stream-ordered reuse).
 // Device scratch: a bump allocator over chunks of at least min_chunk bytes
 // (64 MiB unless given).  A new
@@ -29,12 +40,18 @@ public:
     void reset() { cur_ = 0; off_ = 0; }
     size_t capacity() const;
     bool external() const { return external_; }
+    // what a user of the scratch asks before it takes memory that its call
+    // could do without (nullptr: nobody to ask)
+    void set_grant(MemoryGrant *g) { grant_ = g; }
+    MemoryGrant *grant() const { return grant_; }
+    bool may_take(size_t bytes) { return !grant_ || grant_->take(bytes); }
 
 private:
     std::vector<std::pair<char *, size_t>> chunks_;
     size_t cur_ = 0, off_ = 0;
     size_t min_chunk_;
     bool external_ = false;
+    MemoryGrant *grant_ = nullptr;
 };
 
 // out[i] = sum_{j<i} in[j]; returns nothing, total = out[n-1] + in[n-1].  in == out allowed.

@@ -62,11 +62,25 @@ struct dsd_server_s {
     std::unordered_map<uint64_t, dsd_result> done;
     uint64_t next_ticket = 1;
     int in_flight = 0;     // queued + running
-    size_t running = 0;    // footprints of the groups being run
+    size_t running = 0;    // footprints of the groups being run, and what their calls took besides
     int large_running = 0; // workers holding a large request
     bool stop = false;
     std::vector<std::thread> workers;
     std::vector<hipStream_t> streams;
+
+    // what one group's calls take of the budget beyond its footprint
+    struct Extra final : dsd::MemoryGrant {
+        dsd_server_s *s;
+        size_t taken = 0;
+        explicit Extra(dsd_server_s *srv) : s(srv) {}
+        bool take(size_t bytes) override {
+            std::lock_guard<std::mutex> lk(s->mu);
+            if (s->running > s->budget || bytes > s->budget - s->running) return false;
+            s->running += bytes;
+            taken += bytes;
+            return true;
+        }
+    };
 
     static bool large(const Req &r) { return r.g->g.m >= LARGE_EDGES; }
 
@@ -130,12 +144,14 @@ struct dsd_server_s {
             }
             const int32_t cnt = (int32_t)group.size();
             std::vector<dsd_result> res(cnt);
-            // the group runs on this worker's stream
+            // the group runs on this worker's stream, within the budget
+            Extra extra(this);
             std::vector<hipStream_t> own(cnt);
             for (int32_t i = 0; i < cnt; i++) {
                 own[i] = group[i].g->stream;
                 (void)hipStreamSynchronize(own[i]);
                 group[i].g->stream = ws;
+                group[i].g->sc.set_grant(&extra);
             }
             // requests with host and with device outputs go in two calls
             for (int pass = 0; pass < 2; pass++) {
@@ -161,10 +177,13 @@ struct dsd_server_s {
                 }
             }
             (void)hipStreamSynchronize(ws);
-            for (int32_t i = 0; i < cnt; i++) group[i].g->stream = own[i];
+            for (int32_t i = 0; i < cnt; i++) {
+                group[i].g->stream = own[i];
+                group[i].g->sc.set_grant(nullptr);
+            }
             {
                 std::lock_guard<std::mutex> lk(mu);
-                running -= foot;
+                running -= foot + extra.taken;
                 large_running -= lg ? 1 : 0;
                 for (int32_t i = 0; i < cnt; i++) {
                     state[group[i].ticket] = St::DONE;
