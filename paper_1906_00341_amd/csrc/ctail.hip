@@ -36,14 +36,11 @@ namespace dsd {
 
 namespace {
 
-constexpr int64_t CT_MAX = 131072;             // alive vertices per graph (2,048-word rows: live sets of 16 KB in LDS)
 constexpr int64_t CT_SMALL = 4096;             // up to here a graph of a batch takes a 256-thread workgroup
 constexpr int64_t CT_MID = 32768;              // up to here its waves buffer whole matrix rows in LDS
-constexpr int64_t CT_MATRIX_WORDS = (int64_t)1 << 29;   // all matrices together (4 GiB)
 constexpr int64_t CT_ARENA_WORDS = (int64_t)1 << 25;    // compact rows of one handed-over round (256 MiB), at least
                                                         // one vertex's worth
 constexpr int64_t CT_SHRINK_MIN = 4096;        // a matrix at least this wide is rebuilt once half its vertices are gone
-constexpr int64_t CT_VERTICES = (int64_t)1 << 23;       // vertices of all graphs together (items fit the counter)
 constexpr int CT_ITEM_SHIFT = 40;              // item counter above, task counter below in one 64-bit word
 constexpr u64 CT_TASK_MASK = (1ull << CT_ITEM_SHIFT) - 1ull;
 // One workgroup keeps a round of at most CT_FRONT frontier vertices whose

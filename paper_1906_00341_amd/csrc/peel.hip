@@ -3170,6 +3170,34 @@ __global__ __launch_bounds__(BT) void k_tail_engine(PeelBufs b, const TeGraph *t
     }
 }
 
+// A batch between two rounds: the most alive vertices of one graph, and the
+// words of the graphs' adjacency matrices together (one block).
+struct BatchAlive {
+    i64 most, words;
+};
+__global__ __launch_bounds__(BLOCK) void k_batch_alive(PeelBufs b, BatchAlive *out) {
+    __shared__ i64 sMost[WAVES_PER_BLOCK], sWords[WAVES_PER_BLOCK];
+    i64 most = 0, words = 0;
+    for (int32_t g = threadIdx.x; g < b.G; g += BLOCK) {
+        const i64 a = b.gs[g].n_alive;
+        most = a > most ? a : most;
+        words += a * ((a + 63) / 64);
+    }
+    most = wave_max(most);
+    words = wave_sum(words);
+    if (lane() == 0) {
+        sMost[threadIdx.x / WAVE] = most;
+        sWords[threadIdx.x / WAVE] = words;
+    }
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int i = 1; i < WAVES_PER_BLOCK; i++) {
+        most = sMost[i] > most ? sMost[i] : most;
+        words += sWords[i];
+    }
+    *out = BatchAlive{most, words};
+}
+
 __global__ void k_te_state(TeState *ts, TeState init) { *ts = init; }
 
 // item -> frontier position for a grid round (one wave per frontier vertex)
@@ -3758,11 +3786,26 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     const bool use_graph = pg && pg[0] == '1' && !main_timer.on() && !main2_timer.on();
     RoundGraphs graphs;
     if (use_graph) DSD_HIP(hipStreamCreateWithFlags(&graphs.cs, hipStreamNonBlocking));
+    // A batch's tails are asked once its graphs' sizes allow it, and after a
+    // refusal for other reasons (memory) once half the vertices are gone: an
+    // ask copies every graph's state, at each look of the host at the peel.
+    BatchAlive alive{0, 0};
+    BatchAlive *d_alive = G > 1 && (engine || ctail) ? sc.get_n<BatchAlive>(1) : nullptr;
+    int64_t ask_at = n_alive;
     while (n_alive > 0) {
-        if (engine && (G == 1 ? n_alive <= TE_MAX : steps > 0 && n_alive < (int64_t)G * TE_MAX) &&
-            tail_engine(b, h, n_alive, false, s, sc, kt, nullptr) == 0)
-            break;
-        if (ctail && steps > 0 && G > 1 && clique_tail(b, h, n_alive, s, sc, kt)) break;
+        if (engine && G == 1 && n_alive <= TE_MAX && tail_engine(b, h, n_alive, false, s, sc, kt, nullptr) == 0) break;
+        if (G > 1 && steps > 0 && n_alive <= ask_at) {
+            bool asked = false;
+            if (engine && alive.most <= TE_MAX) {
+                asked = true;
+                if (tail_engine(b, h, n_alive, false, s, sc, kt, nullptr) == 0) break;
+            }
+            if (ctail && n_alive <= CT_VERTICES && alive.most <= CT_MAX && alive.words <= CT_MATRIX_WORDS) {
+                asked = true;
+                if (clique_tail(b, h, n_alive, s, sc, kt)) break;
+            }
+            if (asked) ask_at = n_alive / 2;
+        }
         if (compacting && n_alive < compacted_at / 2) {
             entries = compact_adjacency(b, s, sc);
             compacted_at = n_alive;
@@ -3853,7 +3896,13 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
         }
         if (tail) k_tail_finish<<<1, TAIL_BLOCK, 0, s>>>(b);
         steps += chunk;
-        Readback(sc).add(&n_alive, &b.ctl->n_alive).run(s);
+        Readback rb(sc);
+        rb.add(&n_alive, &b.ctl->n_alive);
+        if (d_alive) {
+            k_batch_alive<<<1, BLOCK, 0, s>>>(b, d_alive);
+            rb.add(&alive, d_alive);
+        }
+        rb.run(s);
         if (steps > max_steps) throw Error(-3, "peel did not converge");
         if (chunk < 32) chunk *= 2;
     }

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 from paper_1906_00341_amd import dsd, synth
-from test_gpu_clique_tail import _cliques
+from test_gpu_clique_tail import _cliques, _dense
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +66,28 @@ def test_matrix_rebuilds_take_no_more_memory(monkeypatch):
     words = n * -(-n // 64)
     need = 8 * 2 * words + 256 * n                   # the first matrix, one vertex's worst case beside it, lists
     assert used["1"] - used["0"] < need + (256 << 20)   # (memory comes in chunks of 64 MiB and more)
+
+
+def test_batch_with_a_graph_above_the_tails_limit():
+    # one graph of more than 131,072 vertices alive for nine rounds, where the
+    # tail cannot take the batch; it takes the others' rounds after those
+    sizes = list(range(5, 13)) * 20 + [13] * 10100
+    made = [_cliques(sizes), _dense(200, 0.5, 3), _cliques(list(range(5, 41)))]
+    alone = []
+    for n, s, d in made[1:]:
+        g = dsd.build_csr(n, s, d)
+        alone.append(dsd.clique_core(g, 4))
+        g.free()
+    gs = [dsd.build_csr(*m) for m in made]
+    outs = [np.zeros(m[0], np.uint64) for m in made]
+    res = dsd.batch_run(gs, 4, "core", outs=outs)
+    dsd.clique_core(gs[1], 4)                        # kept by the batch: its peel's figures
+    assert gs[1].stats()["k4_tail_launches"] > 0
+    for g in gs:
+        g.free()
+    want = np.concatenate([np.full(m, comb(m - 1, 3), np.uint64) for m in sizes])
+    np.testing.assert_array_equal(np.sort(outs[0]), np.sort(want))
+    assert res[0]["kmax"] == comb(12, 3)
+    for (core, km), out, r in zip(alone, outs[1:], res[1:]):
+        np.testing.assert_array_equal(out, core)
+        assert r["kmax"] == km
