@@ -53,7 +53,8 @@ constexpr u64 CT_TASK_MASK = (1ull << CT_ITEM_SHIFT) - 1ull;
 // instead of 0.88 / 3.98 (CoreApp of scale 14 0.51 s instead of 0.15; none of
 // the tail: 3.97 / 8.26 and 0.29); d^4 / 128 and / 256 measure 0.87 and 0.90 s
 // at scale 16, 0.091 and 0.111 at scale 13 (d^4 / 64: 0.085).
-constexpr u64 CT_LIGHT = (u64)CT_ROUND;
+constexpr u64 CT_LIGHT = (u64)CT_ROUND_CYCLES;
+static_assert(CT_LIGHT >= 1000, "a price in cycles (not a phase)");
 constexpr int CT_FRONT = 32;
 // Two waves per SIMD: what every wave does alike (the level, the frontier,
 // the control between barriers) is issued by each of them, so sixteen waves

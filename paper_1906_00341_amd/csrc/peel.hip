@@ -3767,7 +3767,7 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     // (29,340 vertices alive instead of 42,530), 0.96 s of peel instead of 0.92.
     auto ct_light = [&](int64_t alive, int64_t at, int64_t adj) {
         const int64_t d = at > 0 ? adj / at : 0;
-        return alive <= ct_always || d * (alive / WAVE) + d * d / 4 <= CT_ROUND;
+        return alive <= ct_always || d * (alive / WAVE) + d * d / 4 <= CT_ROUND_CYCLES;
     };
     if (ctail && G == 1 && n_alive > 0 && n_alive <= CT_AT_ONCE && clique_tail(b, h, n_alive, s, sc, kt)) n_alive = 0;
     if (compacting && n_alive > 0 && n_alive < n / 2) {

@@ -95,9 +95,9 @@ struct PeelBufs {
 // Finishes the peel of b's graphs (between two rounds) once their alive
 // vertices are few enough for adjacency bitmaps; min_degree as in peel().
 // Returns false, having changed nothing, when they are not (or with
-// DSD_TAIL_ENGINE=0).  CT_ROUND: cycles up to which its workgroup keeps a
+// DSD_TAIL_ENGINE=0).  CT_ROUND_CYCLES: up to these its workgroup keeps a
 // round to itself.
-constexpr int64_t CT_ROUND = 100000;
+constexpr int64_t CT_ROUND_CYCLES = 100000;
 constexpr int64_t CT_MAX = 131072;             // alive vertices per graph (2,048-word rows: live sets of 16 KB in LDS)
 constexpr int64_t CT_MATRIX_WORDS = (int64_t)1 << 29;   // all matrices together (4 GiB)
 constexpr int64_t CT_VERTICES = (int64_t)1 << 23;       // vertices of all graphs together (items fit the counter)
