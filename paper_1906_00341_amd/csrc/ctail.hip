@@ -1510,7 +1510,10 @@ bool clique_tail(const PeelBufs &b, int h, int64_t n_alive, hipStream_t s, Scrat
         // a removed vertex's members with their compact rows, at worst all of its graph
         const int64_t one = widest / 2 + 1 + widest * std::max<int64_t>(8, (widest + 63) / 64);
         if (!q.ctl) {
-            const int64_t acap = std::max<int64_t>(one, std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
+            // DSD_CT_ARENA_WORDS overrides the arena size (0: room for one vertex)
+            const char *aw = std::getenv("DSD_CT_ARENA_WORDS");
+            const int64_t acap = std::max<int64_t>(
+                one, aw ? std::atoll(aw) : std::min<int64_t>(CT_ARENA_WORDS, 16 * words + (1 << 16)));
             size_t free_b = 0, total_b = 0;
             const size_t need = 8 * (size_t)(words + acap + 2 * sets) + 112 * (size_t)total;
             if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need > free_b / 4 || !sc.may_take(need))
