@@ -99,7 +99,8 @@ __device__ __forceinline__ uint32_t csr_cold(uint32_t *cnt, int v, bool cold) {
     u64 left = __ballot(cold);
 #pragma unroll
     for (int l = 0; l < 3; l++) {
-        const u64 m = __ballot(cold && v == __shfl(v, l, WAVE)) & left;
+        const int vl = __shfl(v, l, WAVE);   // (by every lane: lane l need not be cold)
+        const u64 m = __ballot(cold && v == vl) & left;
         if (__popcll(m) < 2) continue;
         const int first = __builtin_ctzll(m);
         uint32_t base = 0;
