@@ -17,8 +17,10 @@
 // its vertices and stops, k_ct_front lists the members of every C_v,
 // k_ct_edges writes its adjacency as compact bitmap rows, k_ct_count counts
 // and takes the losses off the degrees, and the next engine launch ends the
-// round.  The host enqueues these four launches again and again without
-// reading anything back but the number of unfinished graphs now and then.
+// round.  The host enqueues these four launches (five for a batch of small and
+// large graphs, which take an engine of their own size) again and again
+// without reading anything back but the number of unfinished graphs now and
+// then.
 //
 // Owner rule, levels and rounds are those of the round kernels: a round
 // removes every alive vertex of degree <= k; a clique with several of them is
@@ -36,7 +38,7 @@ namespace dsd {
 
 namespace {
 
-constexpr int64_t CT_SMALL = 4096;             // up to here a graph of a batch takes a 256-thread workgroup
+constexpr int64_t CT_SMALL = 4096;             // up to here a graph of a batch takes the workgroup with smaller tables
 constexpr int64_t CT_MID = 32768;              // up to here its waves buffer whole matrix rows in LDS
 constexpr int64_t CT_ARENA_WORDS = (int64_t)1 << 25;    // compact rows of one handed-over round (256 MiB), at least
                                                         // one vertex's worth
@@ -535,7 +537,7 @@ __device__ __forceinline__ int ct_bin(u64 d) {
 __device__ __forceinline__ u64 ct_bin_top(int b) {
     if (b < 16) return (u64)b;
     const int e = b / 8 + 2;
-    return ((u64)(9 + (b & 7)) << (e - 3)) - 1ull;     // (bin 503: the top wraps to 2^64 - 1)
+    return ((u64)(9 + (b & 7)) << (e - 3)) - 1ull;     // (bin 495, the last one a degree has, and 511: 2^64 - 1)
 }
 
 // The edges (x, y), x < y, of the queue's codes (x << 16 | y, members of one

@@ -156,8 +156,9 @@ __device__ u64 bitmap_node_work(int x, const u64 *S, u64 *cnt) {
 // down), operand B moves it to place 3 - s, so that every product is 8.  A is
 // symmetric, so both operands read rows, and the order of the k index does not
 // matter as long as both take the same.  Rows past the last member repeat it;
-// their products meet zero bits only.  Bound by the matrix cores (32 cycles a
-// product, five vector operations beside it).
+// their products meet zero bits only.  Exact: a sum is at most 8 (d - 1)^2,
+// below 2^32 far beyond the 2,048 members of any caller.  Bound by the matrix
+// cores (32 cycles a product, five vector operations beside it).
 typedef int tri_i4 __attribute__((ext_vector_type(4)));
 typedef int tri_i16 __attribute__((ext_vector_type(16)));
 template <int TMAX, class Cnt>
@@ -528,7 +529,7 @@ __global__ __launch_bounds__(BT) void k_engine_rows(Ctx ctx, const int64_t *row_
     __shared__ u64 sTot[NW];
     static_assert((1 << SB) >= CAP && CAP <= 2048, "indexes fit a slot, counters the table");
     uint32_t *cnt = sH;                                // R = 3: the table's space, once it has been used
-    __shared__ uint32_t sCnt2[R == 2 ? CAP : 1];
+    __shared__ uint32_t sCnt2[R == 2 ? CAP : 1];       // (a member's edges: at most CAP - 1)
     const int t = threadIdx.x, wv = t / WAVE, L = lane();
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const int32_t w = ctx.root(it);
