@@ -3761,8 +3761,8 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     // average degree (as many matrix rows of n_alive / 64 words, a quarter of a
     // cycle per pair of members).  Otherwise every round goes to the grid and
     // back: R-MAT scale 22, h = 4, whose alive vertices keep some hundreds of
-    // neighbours each, hands over 64,207 of its 66,404 rounds at 80 us each
-    // (peel 6.0 s without this rule, 4.4 s with it).  The counting (h >= 5:
+    // neighbours each, hands over 64,249 of its 66,448 rounds (peel 5.98 s
+    // without this rule, 3.88 s with it).  The counting (h >= 5:
     // d^3 / 64 more) is left out: R-MAT scale 18, h = 5 enters later with it
     // (29,340 vertices alive instead of 42,530), 0.96 s of peel instead of 0.92.
     auto ct_light = [&](int64_t alive, int64_t at, int64_t adj) {
