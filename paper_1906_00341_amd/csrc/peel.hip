@@ -3786,9 +3786,10 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
     const bool use_graph = pg && pg[0] == '1' && !main_timer.on() && !main2_timer.on();
     RoundGraphs graphs;
     if (use_graph) DSD_HIP(hipStreamCreateWithFlags(&graphs.cs, hipStreamNonBlocking));
-    // A batch's tails are asked once its graphs' sizes allow it, and after a
-    // refusal for other reasons (memory) once half the vertices are gone: an
-    // ask copies every graph's state, at each look of the host at the peel.
+    // A batch's tails are asked once its graphs' sizes allow it, and any tail
+    // after a refusal for other reasons (memory) once half the vertices are
+    // gone: an ask copies every graph's state, at each look of the host at the
+    // peel.
     BatchAlive alive{0, 0};
     BatchAlive *d_alive = G > 1 && (engine || ctail) ? sc.get_n<BatchAlive>(1) : nullptr;
     int64_t ask_at = n_alive;
@@ -3812,9 +3813,11 @@ PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 m
             graphs.reset();
         }
         // (after the compaction: entries is then of at most twice as many vertices)
-        if (ctail && steps > 0 && G == 1 && ct_light(n_alive, compacted_at, entries) &&
-            clique_tail(b, h, n_alive, s, sc, kt))
-            break;
+        if (ctail && steps > 0 && G == 1 && n_alive <= std::min(ask_at, CT_MAX) &&
+            ct_light(n_alive, compacted_at, entries)) {
+            if (clique_tail(b, h, n_alive, s, sc, kt)) break;
+            ask_at = n_alive / 2;
+        }
         if (n_alive <= TAIL_ALIVE) tail = true;
         const int gp = tail ? gtail : gprobe, gq = tail ? gtail : gproc, gf = tail ? gtail : gbuild;
         // one round's kernels; they read the round's state from the device,
