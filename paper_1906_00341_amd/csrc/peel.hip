@@ -3405,8 +3405,8 @@ static void launch_peel_items(const PeelBufs &b, hipStream_t s, u64 *gS, int32_t
 // fit, or no graph (or not every one, between rounds) is small enough; the
 // environment variable DSD_TAIL_ENGINE=0 turns it off.  max_round (nullable):
 // the largest round count of the graphs taken.
-static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_start, hipStream_t s, Scratch &sc,
-                           KernelTimes *kt, int32_t *max_round) {
+static int64_t tail_engine_run(const PeelBufs &b, int h, int64_t n_alive, bool at_start, hipStream_t s, Scratch &sc,
+                               KernelTimes *kt, int32_t *max_round) {
     const char *env = std::getenv("DSD_TAIL_ENGINE");
     if (env && std::strcmp(env, "0") == 0) return -1;
     const int32_t n = b.n;
@@ -3579,6 +3579,19 @@ static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_st
         kt->tail_grid_pairs += hts.pairs;
     }
     return left;
+}
+
+static int64_t tail_engine(const PeelBufs &b, int h, int64_t n_alive, bool at_start, hipStream_t s, Scratch &sc,
+                           KernelTimes *kt, int32_t *max_round) {
+    try {
+        return tail_engine_run(b, h, n_alive, at_start, s, sc, kt, max_round);
+    } catch (const Error &e) {
+        // another stream's work took the memory meanwhile (everything is
+        // allocated before the engine starts): the round kernels go on
+        if (e.status != -2 || sc.external()) throw;
+        (void)hipGetLastError();
+        return -1;
+    }
 }
 
 PeelResult peel(const DevGraph &g, int h, const uint8_t *alive0, u64 *deg, u64 mu, u64 k_floor, u64 *core,
