@@ -19,7 +19,7 @@ Further legs: the Chung-Lu graph (n = 10^6, h = 3, where CoreExact runs to
 the end), the batched mixture (8,192 graphs, batched vs a plain per-graph
 loop), the server under load, the CPU oracle on a bounded sample of the
 headline family and the OpenMP enumeration beside it, and the same R-MAT
-graph at h = 5: one step (about 80 s), without warm-up or per-launch
+graph at h = 5: one step (about 50 s), without warm-up or per-launch
 timing.
 
 Prints one JSON line.  ``value`` is whole-pass throughput in h-cliques/s
